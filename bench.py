@@ -25,7 +25,8 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, 8 TB/s
 BYTES_PER_POP = {"fp64": 8, "fp32": 4, "fp16s": 2, "bf16s": 2}
-KERNEL_SRC = os.path.join(ROOT, "paper_2508_13867_amd", "csrc", "lbm_kernels.hip")
+KERNEL_SRC = [os.path.join(ROOT, "paper_2508_13867_amd", "csrc", f)
+              for f in ("lbm_device.h", "fused_shapes.h", "fused_kernels.hip")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_stream_collide_tgv256_fp32.json")
 VALU_FILE = os.path.join(ROOT, "profiles", "valu_k_stepR_tgv256_fp32.json")
 VALU_ISSUE_PER_S = 256 * 2.4e9  # one wave64 VALU instruction per CU and cycle
@@ -36,8 +37,11 @@ def log(*a):
 
 
 def kernel_hash():
-    with open(KERNEL_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for path in KERNEL_SRC:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def measured_traffic(kernel_prefix):

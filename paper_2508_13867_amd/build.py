@@ -14,8 +14,13 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libuqlbm.so")
-SOURCES = ["sampler.cpp", "uq_api.cpp", "engine.cpp", "tuner.cpp", "server.cpp", "lbm_kernels.hip",
-           "wasserstein.hip", "noalloc.hip"]
+# (source, flags, object); the temporally blocked kernels are compiled once
+# per storage precision
+UNITS = [(s, [], os.path.splitext(s)[0] + ".o")
+         for s in ("sampler.cpp", "uq_api.cpp", "engine.cpp", "tuner.cpp", "server.cpp", "lbm_kernels.hip",
+                   "wasserstein.hip", "noalloc.hip")]
+UNITS += [(s, [f"-DUQ_PREC={p}"], os.path.splitext(s)[0] + f"_p{p}.o")
+          for s in ("fused_kernels.hip",) for p in range(4)]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 FLAGS = [
@@ -29,10 +34,10 @@ def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     procs = []
     objs = []
-    for src in SOURCES:
-        obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
+    for src, defs, name in UNITS:
+        obj = os.path.join(BUILD, name)
         objs.append(obj)
-        cmd = [HIPCC, *FLAGS, "-I", CSRC, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [HIPCC, *FLAGS, *defs, "-I", CSRC, "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))

@@ -18,6 +18,31 @@ static int env_int(const char *name, int dflt) {
     return std::atoi(v);
 }
 
+// The chunk count that minimises rounds of work items x row steps per item: a
+// last round that leaves most CUs idle costs as much as a full one, and every
+// chunk pays the pipeline's fill, so neither short nor tall chunks are best
+// by themselves (1024^2 x 16 samples, 9 strips, 8 steps per launch: chunks of
+// 32, 64, 128, 256 rows took 50.2, 44.1, 44.7, 52.4 us per step, in the
+// ratios of this count). Items that have a CU to themselves run faster: a
+// round that gives each CU at most one counts 0.6.
+int chunk_rows(int ny, int64_t items, int fill, int per_cu) {
+    const int64_t slots = (int64_t)256 * per_cu;
+    double best = 0.0;
+    int rows = ny;
+    for (int c = 1; c <= std::max(1, ny / 8); ++c) {
+        const int H = (ny + c - 1) / c;
+        const int64_t n = items * ((ny + H - 1) / H);
+        const int64_t rest = n % slots;
+        const double rounds = (double)(n / slots) + (rest == 0 ? 0.0 : (rest <= 256 && per_cu > 1 ? 0.6 : 1.0));
+        const double cost = rounds * (H + fill);
+        if (c == 1 || cost < 0.999 * best) {
+            best = cost;
+            rows = H;
+        }
+    }
+    return std::max(8, rows);
+}
+
 // Launch shape and layout of a job. Order of precedence: a shape measured by
 // uq_autotune for this problem class (when the problem leaves the layout to
 // AUTO, or fixes the same layout), then the UQ_* environment overrides, then
@@ -82,7 +107,8 @@ int Job::fused_n() const {
                 jd.nx <= channel_rows_max_nx(jd.prec, shape.fuse))
                    ? shape.fuse
                    : 0;
-    const int nmax = shape.fwin == 2 ? 8 : 4;  // whole rows: up to 8 steps
+    const int nmax = shape.fwin >= 2 ? 8 : 4;  // whole rows and their strips: up to 8 steps
+    if (shape.fwin == 3 && shape.fuse < 3) return 0;
     return (shape.fuse <= nmax && fused_supported(jd)) ? shape.fuse : 0;
 }
 

@@ -129,7 +129,8 @@ static size_t up256(size_t n) { return (n + 255) / 256 * 256; }
 // 0) and channels whose boundary rules are node-local (kind 1: half-way
 // walls and cylinder, Zou-He or wall or periodic ends) advance N steps per
 // launch over whole rows of H-row chunks in the AB layout; vortex lattices
-// too wide for whole rows, 4 steps per launch in strips (kind 2); kind -1:
+// too wide for whole rows at 8 steps, 8 steps per launch in strips of rows
+// (kind 2); kind -1:
 // one step per launch in the AA layout (the batched single-step kernel). A shape the
 // launch-shape tuner measured for the job's class is taken when it is a
 // batched instance; otherwise N is the largest of the instance's choices
@@ -159,7 +160,7 @@ static ServeShape serve_shape(const uq_problem &p, int64_t S, int K, size_t aren
     // fastest at 6 steps per launch, wider ones at 8 (measured per width on
     // the serving mix); channels take the deepest pipeline that fits
     const bool narrow = p.nx <= 128;
-    const int pref[2][3] = {{narrow ? 6 : 8, narrow ? 8 : 6, 4}, {4, 3, 2}};
+    const int pref[2][3] = {{narrow ? 6 : 8, narrow ? 8 : 0, 0}, {4, 3, 2}};
     StepShape tuned;
     const bool have = tuned_shape(p, S, &tuned) && tuned.fwin == 2 && tuned.fuse >= 2;
     for (int c = -1; c < 3; ++c) {
@@ -185,16 +186,18 @@ static ServeShape serve_shape(const uq_problem &p, int64_t S, int K, size_t aren
         }
         return sh;
     }
-    // vortex rows too wide for any whole-row instance: 4 steps per launch
-    // in strips of 32-row chunks, if the job's two slabs take at most two
-    // fifths of the arena (a larger job would hold back every other
-    // admission; it runs in AA). (32 rows ran the serving mix's strip jobs
-    // 4 % faster than 64: more, shorter work items.)
-    if (kind == 0 && (size_t)job_footprint(p, S, K, true) <= arena * 2 / 5) {
+    // vortex rows too wide for 8 steps over whole rows: 8 steps per launch in
+    // strips (k_stepRS; 384^2 x 256 samples: 360k MLUPS against 275k for 4
+    // steps over whole rows, 1024^2 x 64: 414k against 234k for 4 steps in
+    // single-wave strips). Beyond 512 columns only if the job's two slabs
+    // take at most two fifths of the arena (a larger job would hold back
+    // every other admission; it runs in AA).
+    if (kind == 0 && (p.nx <= 512 || (size_t)job_footprint(p, S, K, true) <= arena * 2 / 5)) {
         sh.kind = 2;
-        sh.N = 4;
-        sh.H = std::max(8, std::min(32, p.ny));
-        window_strips(p.nx, sh.N, &sh.W, &sh.strips);
+        sh.N = 8;
+        const int chunks = (p.ny + 127) / 128;
+        sh.H = std::max(8, (p.ny + chunks - 1) / chunks);
+        row_strips(p.precision, p.nx, sh.N, &sh.W, &sh.strips);
     }
     return sh;
 }
@@ -342,7 +345,7 @@ void Server::admit() {
         if (r.shape.kind >= 0) {
             sh.layout = UQ_LAYOUT_AB;
             sh.fuse = r.shape.N;
-            sh.fwin = r.shape.kind == 2 ? 1 : 2;
+            sh.fwin = r.shape.kind == 2 ? 3 : 2;
             sh.fty = r.shape.H;
         } else {
             sh.layout = UQ_LAYOUT_AA;
@@ -467,8 +470,7 @@ uq_status Server::rebuild_table() {
     }
     // an instance whose jobs give fewer work items than the GPU has CUs
     // takes shorter row chunks: more items, each a shorter pipeline (the
-    // extra halo rows cost less than idle CUs). The chunking does not change
-    // any node's arithmetic.
+    // extra halo rows cost less than idle CUs). The chunking does not change any node's arithmetic.
     constexpr int64_t kTargetItems = 256;
     for (Group &g : groups) {
         if (g.kind == 2 || g.nwork >= kTargetItems) continue;

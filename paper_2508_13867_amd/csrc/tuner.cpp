@@ -174,6 +174,24 @@ extern "C" uq_status uq_autotune(const uq_problem *p, const uq_device *dev, int6
                         cands.push_back(s);
                     }
         }
+        // rows wider than 8 steps over whole rows take: the same pipeline down
+        // strips, 6 or 8 steps per launch
+        if (layout == UQ_LAYOUT_AB && p->geometry == UQ_GEOM_TGV && p->nx > 256)
+            for (int n : {6, 8}) {
+                int W, strips;
+                row_strips(p->precision, p->nx, n, &W, &strips);
+                std::vector<int> heights = {64, 256, chunk_rows(p->ny, r.S * strips, 3 * (n - 1), 2)};
+                for (int fty : heights) {
+                    StepShape s;
+                    s.layout = layout;
+                    s.pad = 64;
+                    s.nt = 0;
+                    s.fuse = n;
+                    s.fty = fty;
+                    s.fwin = 3;
+                    cands.push_back(s);
+                }
+            }
     }
 
     const double bytes_per_node = 18.0 * (double)storage_bytes(p->precision);

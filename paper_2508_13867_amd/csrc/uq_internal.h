@@ -144,7 +144,8 @@ struct StepShape {
     int bx = 64;        // workgroup width along x (64, 128 or 256; height 256/bx)
     int fuse = 0;       // periodic AB jobs: steps per launch of k_stepN (2..4; 0, 1: k_step)
     int fty = 8;        // k_stepN tile height (rows of 64 output nodes); k_stepW chunk rows
-    int fwin = 0;       // fused kernel: 0 tiles (k_stepN), 1 sliding window (k_stepW), 2 full rows (k_stepR)
+    int fwin = 0;       // fused kernel: 0 tiles (k_stepN), 1 sliding window (k_stepW), 2 full rows (k_stepR),
+                        // 3 strips of rows (k_stepRS)
 };
 
 // one stream-collide step for all samples at time t = *d_t + k; `parity`
@@ -163,7 +164,8 @@ hipError_t launch_step(const JobDev &j, const int64_t *d_t, int k, int parity, c
 // read from slab f2 if src2 else f and n steps later written to the other
 // slab (the host keeps the slab of each step's state; see Job::enqueue_steps)
 // (window 1: the sliding-window kernel with chunks of fty rows, its stores
-// non-temporal if nt; 2: the same over whole rows; 0: the 64 x fty tile kernel)
+// non-temporal if nt; 2: the same over whole rows; 3: the whole-row pipeline
+// down strips; 0: the 64 x fty tile kernel)
 // (channel jobs: window 2 only, advancing the steps t = *d_t + k ..; see
 // channel_fusable)
 hipError_t launch_fused(const JobDev &j, int n, bool src2, int fty, int window, bool nt, const int64_t *d_t, int k,
@@ -178,16 +180,17 @@ int full_rows_max_nx(int prec, int n);
 bool fused_supported(const JobDev &j);
 // Batched fused launches (continuous batching with temporal blocking).
 // kind 0: periodic lattice over whole rows, kind 1: channel over whole rows,
-// kind 2: periodic lattice in strips of at most 64 - 2(N - 1) columns (any
-// width). rows_instance gives the waves per level K and columns per lane M
+// kind 2: periodic lattice in strips of whole-row pipelines (any width).
+// rows_instance gives the waves per level K and columns per lane M
 // of the N-step whole-row instance for rows nx wide (0 if none fits);
 // fused_multi_supported says whether the batched form of an instance exists
-// (N in {4, 6, 8} periodic rows, {2, 3, 4} channel rows, 4 strips; single-
-// precision storage formats). window_strips gives the strips per row and
-// their width for N steps.
+// (N in {4, 6, 8} periodic rows, {2, 3, 4} channel rows, 8 strips; single-
+// precision storage formats). row_strips gives the strips per row and their
+// width (balanced) for n steps per launch.
 int rows_instance(int kind, int prec, int n, int nx, int *K, int *M);
 bool fused_multi_supported(int kind, int prec, int n, int K, int M);
 void window_strips(int nx, int n, int *W, int *strips);
+void row_strips(int prec, int nx, int n, int *W, int *strips);
 // launch number `launch` of a tick: every work item of jobs[0..njobs)
 hipError_t launch_fused_multi(int kind, int prec, int n, int K, int M, const FusedJob *jobs, int njobs,
                               int64_t nwork, int launch, hipStream_t s);
