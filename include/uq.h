@@ -53,7 +53,8 @@ typedef enum {
  * rounding). AA: one slab updated in place (AA access pattern). AB: two slabs,
  * pull from one and write aligned to the other (twice the memory, higher
  * HBM rate on MI355X). AUTO: the launch-shape tuner's choice for the
- * problem class (AA unless a measured AB entry exists or UQ_LAYOUT is set). */
+ * problem class; without one, AB where a pipeline of several steps per launch
+ * carries the job (and both slabs find room), else AA; UQ_LAYOUT overrides. */
 typedef enum { UQ_LAYOUT_AUTO = 0, UQ_LAYOUT_AA = 1, UQ_LAYOUT_AB = 2 } uq_layout;
 
 /* Deterministic problem solved for every sample. */
@@ -312,8 +313,9 @@ uq_status uq_samples(const uq_job *job, double *xi, double *a, int64_t *S, int32
 
 /* Advance all samples by `steps` LBM steps (stream + collide with the
  * boundaries inline). Every launch advances all samples: one step per launch,
- * or, in the fused shapes the tuner picks for periodic lattices and simple
- * channels in the AB layout, N = 2..8 steps per launch (temporal blocking).
+ * or, in the fused shapes that periodic lattices take by themselves and the
+ * tuner picks for them and for simple channels in the AB layout, N = 2..8
+ * steps per launch (temporal blocking).
  * Whole blocks of fused launches are replayed from a captured hipGraph; the
  * steps left over run as launches of an odd number (3 or more, at most N) of
  * fused steps, largest first, and the last one or two as single steps, so

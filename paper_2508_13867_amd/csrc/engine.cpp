@@ -8,6 +8,7 @@
 #include <cstdlib>
 #include <string>
 
+#include "fused_shapes.h"
 #include "uq_job.h"
 
 namespace uqi {
@@ -43,16 +44,72 @@ int chunk_rows(int ny, int64_t items, int fill, int per_cu) {
     return std::max(8, rows);
 }
 
+// Workgroups of a row pipeline that a CU holds: by its LDS rings (160 KB) and
+// by its waves' registers. The compiler's counts: single precision 60 VGPRs
+// with one column per lane (28 waves per CU) and 101-111 with two (16),
+// double precision 110 (16) and 188-197 (8); the channel's 90-98 (20), 135-145
+// (12), 147-193 (8) and 235-247 (8).
+static int pipeline_per_cu(int prec, int n, int rows, int K, int M) {
+    const bool ch = rows == RING_ROWS_CH, dbl = prec == UQ_FP64;
+    const int waves = M == 1 ? (dbl ? (ch ? 8 : 16) : (ch ? 20 : 28)) : (dbl ? 8 : (ch ? 12 : 16));
+    const int64_t lds = (int64_t)(n - 1) * rows * ring_cols(rows, K, M) * (dbl ? 8 : 4);
+    return (int)std::max<int64_t>(1, std::min<int64_t>(waves / (n * K), 160 * 1024 / lds));
+}
+
+// The pipeline that carries a job whose shape and layout nobody chose, if one
+// does (AB layout). Periodic lattices, always: 8 steps per launch over whole rows where
+// the LDS rings hold them, else in strips; up to 128 columns 6 steps (one
+// column per lane; two workgroups per CU in single precision, and the deepest
+// that double precision's rings hold) unless so few samples ask for it that
+// every chunk gets a CU of its own. Against one step per launch, in us per
+// step: FP64 64^2 x 5 samples 2.91 -> 2.38, 64^2 x 64 6.28 -> 3.39, FP32 96^2
+// x 3 2.53 -> 1.99, 128^2 x 135 23.5 -> 8.0, 1024^2 x 16 238 -> 44.
+static bool default_pipeline(const uq_problem &p, int64_t S, StepShape *s) {
+    if (p.geometry != UQ_GEOM_TGV || p.layout != UQ_LAYOUT_AUTO) return false;
+    const int64_t plane = (int64_t)p.ny * row_pitch(p.nx) + 64;
+    const int64_t b = storage_bytes(p.precision), slab = S * 9 * plane * b;
+    if (9 * plane * b >= ((int64_t)1 << 31)) return false;
+    // the second slab may take a quarter of the card: a job that only just
+    // fits keeps to one
+    if (slab > ((int64_t)72 << 30)) return false;
+    s->layout = UQ_LAYOUT_AB;
+    s->pad = 64;
+    s->nt = 0;
+    int K = 0, M = 0;
+    s->fuse = p.nx > 128 ? 8 : (p.precision != UQ_FP64 && S * p.ny <= 256 * 12 ? 8 : 6);
+    if (rows_shape(p.precision, s->fuse, RING_ROWS_TGV, p.nx, &K, &M)) {
+        s->fwin = 2;
+        s->fty = chunk_rows(p.ny, S, 3 * (s->fuse - 1), pipeline_per_cu(p.precision, s->fuse, RING_ROWS_TGV, K, M));
+    } else {
+        int W, strips;
+        row_strips(p.precision, p.nx, s->fuse, &W, &strips);
+        s->fwin = 3;
+        s->fty = chunk_rows(p.ny, S * strips, 3 * (s->fuse - 1),
+                            pipeline_per_cu(p.precision, s->fuse, RING_ROWS_TGV, RowStrips<UQ_FP32>::K,
+                                            RowStrips<UQ_FP32>::M));
+    }
+    return true;
+}
+
 // Launch shape and layout of a job. Order of precedence: a shape measured by
 // uq_autotune for this problem class (when the problem leaves the layout to
 // AUTO, or fixes the same layout), then the UQ_* environment overrides, then
-// the defaults (AA, one row per thread, 64 elements of plane padding).
-StepShape choose_shape(const uq_problem &p, int64_t S) {
+// the pipeline that suits the problem, then one step per launch (AA, one row
+// per thread, 64 elements of plane padding).
+StepShape choose_shape(const uq_problem &p, int64_t S, bool pipelines) {
     StepShape s;
     if (tuned_shape(p, S, &s)) {
         if (needs_ab(p)) s.layout = UQ_LAYOUT_AB;
         return s;
     }
+    bool asked = false;
+    for (const char *name : {"UQ_CPT", "UQ_PERSISTENT", "UQ_NT_STORE", "UQ_PLANE_PAD", "UQ_BX", "UQ_FUSE",
+                             "UQ_FUSE_TY", "UQ_FUSE_WINDOW", "UQ_LAYOUT"}) {
+        const char *v = std::getenv(name);
+        asked = asked || (v && *v);
+    }
+    if (pipelines && !asked && default_pipeline(p, S, &s)) return s;
+    s = StepShape();
     s.cpt = env_int("UQ_CPT", 1);
     s.persistent = env_int("UQ_PERSISTENT", 0);
     s.nt = env_int("UQ_NT_STORE", 1);

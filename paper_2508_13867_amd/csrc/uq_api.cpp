@@ -275,17 +275,30 @@ uq_status create_job(const uq_problem &prob, const uq_device *dev, const StepSha
         return fail(UQ_EINVAL, "interpolated boundaries need the AB layout");
     // padding after each population plane (elements, multiple of 64): spreads
     // the nine plane streams of a wavefront over HBM channels
+    auto slabs = [&](void **slab, void **slab2) {
+        const int64_t pad = std::max(0, j->shape.pad) / 64 * 64;
+        const int64_t plane = (int64_t)P.ny * j->pitch + pad;
+        const size_t bytes = (size_t)(j->S * 9 * plane * storage_bytes(P.precision));
+        *slab = j->dalloc(bytes);
+        *slab2 = *slab && j->shape.layout == UQ_LAYOUT_AB ? j->dalloc(bytes) : nullptr;
+    };
+    void *slab = nullptr, *slab2 = nullptr;
+    slabs(&slab, &slab2);
+    if (j->shape.layout == UQ_LAYOUT_AB && !slab2 && !forced && P.layout == UQ_LAYOUT_AUTO) {
+        // no room for the second slab that a pipeline would have liked
+        const StepShape one = choose_shape(P, j->S, false);
+        if (one.layout != UQ_LAYOUT_AB) {
+            j->dfree_all();
+            j->shape = one;
+            slabs(&slab, &slab2);
+        }
+    }
     const int64_t pad = std::max(0, j->shape.pad) / 64 * 64;
     const int64_t plane = (int64_t)P.ny * j->pitch + pad;
     const int64_t slab_bytes = j->S * 9 * plane * storage_bytes(P.precision);
-    void *slab = j->dalloc((size_t)slab_bytes);
-    void *slab2 = nullptr;
-    if (j->shape.layout == UQ_LAYOUT_AB) {
-        slab2 = j->dalloc((size_t)slab_bytes);
-        if (!slab2) {
-            j->dfree_all();
-            return fail(UQ_ENOMEM, "out of device memory for the second slab (" + std::to_string(slab_bytes) + " B)");
-        }
+    if (slab && j->shape.layout == UQ_LAYOUT_AB && !slab2) {
+        j->dfree_all();
+        return fail(UQ_ENOMEM, "out of device memory for the second slab (" + std::to_string(slab_bytes) + " B)");
     }
     SampleDev *d_smp = (SampleDev *)j->dalloc(sizeof(SampleDev) * j->S);
     j->d_t = (int64_t *)j->dalloc(sizeof(int64_t));

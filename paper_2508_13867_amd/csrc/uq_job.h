@@ -14,7 +14,9 @@ int64_t storage_bytes(int prec);
 int64_t row_pitch(int nx);
 void build_mask(const uq_problem &p, int64_t pitch, std::vector<uint32_t> &mask, std::vector<double> &q,
                 std::vector<int32_t> &special, int &fluid);
-StepShape choose_shape(const uq_problem &p, int64_t S);
+// pipelines = false: without the pipelines that take a second slab on their
+// own account
+StepShape choose_shape(const uq_problem &p, int64_t S, bool pipelines = true);
 // Rows per chunk of a pipelined launch: `items` work items per chunk of rows,
 // of which `per_cu` fit a CU, `fill` row steps to fill and drain a pipeline.
 int chunk_rows(int ny, int64_t items, int fill, int per_cu);
