@@ -295,23 +295,42 @@ struct NSum {
         c += (fabs(s) >= fabs(x)) ? ((s - t) + x) : ((x - t) + s);
         s = t;
     }
+    // another sum's terms
+    __device__ inline void join(double os, double oc) {
+        add(os);
+        c += oc;
+    }
     __device__ inline double val() const { return s + c; }
 };
 
-// One workgroup per sample: KE, momentum-exchange force, non-finite count.
+// The sums of a wave's 64 lanes, joined in a fixed tree: whole in lane 0.
+__device__ inline void wave_join(NSum &a) {
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) a.join(__shfl_down(a.s, d), __shfl_down(a.c, d));
+}
+
+// KE, momentum-exchange force and non-finite count of a sample, or of one of
+// its chunks of `per` nodes: workgroup (chunk, sample). A job with fewer
+// samples than the card takes workgroups is cut into chunks, whose sums go to
+// part[sample][chunk] = {KE, Fx, Fy as sum and compensation, count} and are
+// joined by k_qoi_join (one workgroup per sample read 1024^2 nodes x 16
+// samples in 3.2 ms, 0.2 TB/s; latency bound).
+constexpr int QOI_PART = 7;
 template <int P, bool CHANNEL, int MODE>
-__global__ __launch_bounds__(256) void k_qoi(JobDev j, int64_t t, double *out) {
+__global__ __launch_bounds__(256) void k_qoi(JobDev j, int64_t t, int per, double *part, double *out) {
     using PR = Prec<P>;
     using C = typename PR::C;
     using T = typename PR::T;
-    const int64_t smp = blockIdx.x;
+    const int64_t smp = (int64_t)blockIdx.y * gridDim.z + blockIdx.z;
+    if (smp >= j.S) return;
     const T *base = (const T *)(MODE == AB_PULL && (t & 1) ? j.f2 : j.f) + smp * 9 * j.plane;
     const SampleDev sd = j.smp[smp];
     NSum ke, fx, fy;
     double bad = 0.0;
-    const int64_t cells = (int64_t)j.nx * j.ny;
-    for (int64_t c = threadIdx.x; c < cells; c += blockDim.x) {
-        const int y = (int)(c / j.nx), x = (int)(c - (int64_t)y * j.nx);
+    const uint32_t nx = (uint32_t)j.nx, first = blockIdx.x * (uint32_t)per;
+    const uint32_t end = min(nx * (uint32_t)j.ny, first + (uint32_t)per);
+    for (uint32_t c = first + threadIdx.x; c < end; c += blockDim.x) {
+        const int y = (int)(c / nx), x = (int)(c - (uint32_t)y * nx);
         uint32_t m = 0;
         if (CHANNEL) {
             m = j.mask[(int64_t)y * j.pitch + x];
@@ -354,19 +373,36 @@ __global__ __launch_bounds__(256) void k_qoi(JobDev j, int64_t t, double *out) {
         if (!isfinite(dux) || !isfinite(duy) || !isfinite((double)drho)) bad += 1.0;
         ke.add(dux * dux + duy * duy);
     }
-    // fixed-order block reduction (deterministic)
-    __shared__ double red[4][256];
-    red[0][threadIdx.x] = ke.val();
-    red[1][threadIdx.x] = fx.val();
-    red[2][threadIdx.x] = fy.val();
-    red[3][threadIdx.x] = bad;
+    // a fixed tree over the lanes, then the waves in order (deterministic)
+    __shared__ double red[4][QOI_PART];
+    wave_join(ke);
+    if (CHANNEL) {
+        wave_join(fx);
+        wave_join(fy);
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) bad += __shfl_down(bad, d);
+    if ((threadIdx.x & 63) == 0) {
+        double *r = red[threadIdx.x >> 6];
+        r[0] = ke.s, r[1] = ke.c, r[2] = fx.s, r[3] = fx.c, r[4] = fy.s, r[5] = fy.c, r[6] = bad;
+    }
     __syncthreads();
-    if (threadIdx.x < 4) {
-        NSum acc;
-        for (int k = 0; k < (int)blockDim.x; ++k) acc.add(red[threadIdx.x][k]);
-        double v = acc.val();
-        if (threadIdx.x == 0) v *= j.ke_norm;
-        out[smp * 4 + threadIdx.x] = v;
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 4; ++w) {
+            ke.join(red[w][0], red[w][1]);
+            fx.join(red[w][2], red[w][3]);
+            fy.join(red[w][4], red[w][5]);
+            bad += red[w][6];
+        }
+        if (gridDim.x > 1) {
+            double *q = part + (smp * gridDim.x + blockIdx.x) * QOI_PART;
+            q[0] = ke.s, q[1] = ke.c, q[2] = fx.s, q[3] = fx.c, q[4] = fy.s, q[5] = fy.c, q[6] = bad;
+        } else {
+            out[smp * 4] = ke.val() * j.ke_norm;
+            out[smp * 4 + 1] = fx.val();
+            out[smp * 4 + 2] = fy.val();
+            out[smp * 4 + 3] = bad;
+        }
     }
 }
 
@@ -436,9 +472,9 @@ __global__ __launch_bounds__(256) void k_export(JobDev j, int64_t t, int64_t smp
 // Statistics of a field QoI read straight from the populations, without a
 // per-sample field buffer: the value of a (sample, node) is formed from its
 // pulled populations exactly as k_fields forms it (velocity u_x, u_y; density
-// 1 + drho; speed |u|; 0 at solid nodes), and every sum over the samples runs
-// in ascending sample order with Neumaier compensation (FP64), output by
-// output, so the result does not depend on the launch shape.
+// 1 + drho; speed |u|; 0 at solid nodes), and every sum over the samples is
+// Neumaier-compensated (FP64) in an order fixed by the lattice and the sample
+// count.
 // Field QoIs: which = 0 velocity (two components), 1 density, 2 speed.
 constexpr int FP_JB = 16;  // samples per LDS block of values
 constexpr int FP_KA = 12;  // (component, coefficient) pairs per thread
@@ -447,7 +483,7 @@ template <int P, bool CHANNEL, int MODE>
 __device__ inline void field_value(const JobDev &j, const typename Prec<P>::T *base, int64_t t, int64_t smp,
                                    int64_t c, int which, double &v0, double &v1) {
     using C = typename Prec<P>::C;
-    const int y = (int)(c / j.nx), x = (int)(c - (int64_t)y * j.nx);
+    const int y = (int)((uint32_t)c / (uint32_t)j.nx), x = (int)c - y * j.nx;
     uint32_t m = 0;
     v0 = v1 = 0.0;
     if (CHANNEL) {
@@ -520,25 +556,54 @@ __global__ __launch_bounds__(256) void k_field_coeffs(JobDev j, int64_t t, int w
     }
 }
 
-// The rest of a field's statistics, one thread per node (both velocity
-// components): SC (wphi != null): mean = c_0, var = sum_{k>=1} c_k^2 (Eq.
-// gpc_std) and the quadrature variance sum_j a_j (M_j - mean)^2; MC: mean
-// (Eq. meanMCS), var with 1/(N-1) (Eq. varMCS) and 1/N, two passes.
+// The rest of a field's statistics (both velocity components of a node at
+// once): SC (wphi != null): mean = c_0, var = sum_{k>=1} c_k^2 (Eq. gpc_std)
+// and the quadrature variance sum_j a_j (M_j - mean)^2; MC: mean (Eq.
+// meanMCS), var with 1/(N-1) (Eq. varMCS) and 1/N, two passes.
+// A workgroup takes 64 nodes, one per lane; its G = blockDim / 64 waves take
+// every G-th sample and their sums are joined in order, so the result depends
+// on G (the lattice and the sample count) only within the compensation. With
+// one thread per node over all samples a 128^2 lattice gave 64 workgroups, each
+// a serial chain of 2 x 4096 gathers: 5.5 ms for 2 x 0.6 GB.
+constexpr int FF_MAX_G = 16;
 template <int P, bool CHANNEL, int MODE>
-__global__ __launch_bounds__(256) void k_field_finish(JobDev j, int64_t t, int which, const double *__restrict__ a,
-                                                      int K, const double *coeffs, double *mean, double *var,
-                                                      double *var_alt) {
+__global__ __launch_bounds__(64 * FF_MAX_G) void k_field_finish(JobDev j, int64_t t, int which,
+                                                                const double *__restrict__ a, int K,
+                                                                const double *coeffs, double *mean, double *var,
+                                                                double *var_alt) {
     using T = typename Prec<P>::T;
+    __shared__ double red[FF_MAX_G][4][64];
     const int64_t cells = (int64_t)j.nx * j.ny;
     const int comps = which == 0 ? 2 : 1;
     const int64_t n_out = comps * cells;
+    const int lane = threadIdx.x & 63, G = blockDim.x >> 6;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t c = (int64_t)blockIdx.x * 64 + lane;
+    const bool on = c < cells;
     const T *slab = (const T *)(MODE == AB_PULL && (t & 1) ? j.f2 : j.f);
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < cells; c += (int64_t)gridDim.x * blockDim.x) {
-        double mu[2] = {0.0, 0.0};
-        if (K > 0) {
+    // the waves' sums of two quantities, joined: the same in every wave
+    auto join = [&](const NSum *s, double *v) {
+        red[w][0][lane] = s[0].s;
+        red[w][1][lane] = s[0].c;
+        red[w][2][lane] = s[1].s;
+        red[w][3][lane] = s[1].c;
+        __syncthreads();
+        NSum a0, a1;
+        for (int g = 0; g < G; ++g) {
+            a0.join(red[g][0][lane], red[g][1][lane]);
+            a1.join(red[g][2][lane], red[g][3][lane]);
+        }
+        v[0] = a0.val();
+        v[1] = a1.val();
+        __syncthreads();
+    };
+    double mu[2] = {0.0, 0.0};
+    if (K > 0) {
+        if (on)
             for (int q = 0; q < comps; ++q) {
                 const int64_t o = q * cells + c;
                 mu[q] = coeffs[o];
+                if (w != 0) continue;
                 NSum v;
                 for (int k = 1; k < K; ++k) {
                     const double ck = coeffs[(int64_t)k * n_out + o];
@@ -547,40 +612,46 @@ __global__ __launch_bounds__(256) void k_field_finish(JobDev j, int64_t t, int w
                 mean[o] = mu[q];
                 var[o] = v.val();
             }
-        } else {
-            NSum s0, s1;
-            for (int64_t smp = 0; smp < j.S; ++smp) {
+    } else {
+        NSum s[2];
+        if (on)
+#pragma unroll 2
+            for (int64_t smp = w; smp < j.S; smp += G) {
                 double v0, v1;
                 field_value<P, CHANNEL, MODE>(j, slab + smp * 9 * j.plane, t, smp, c, which, v0, v1);
-                s0.add(v0);
-                s1.add(v1);
+                s[0].add(v0);
+                s[1].add(v1);
             }
-            mu[0] = s0.val() / (double)j.S;
-            mu[1] = s1.val() / (double)j.S;
-        }
-        NSum q0, q1;
-        for (int64_t smp = 0; smp < j.S; ++smp) {
+        join(s, mu);
+        mu[0] /= (double)j.S;
+        mu[1] /= (double)j.S;
+    }
+    NSum q[2];
+    if (on)
+#pragma unroll 2
+        for (int64_t smp = w; smp < j.S; smp += G) {
             double v0, v1;
             field_value<P, CHANNEL, MODE>(j, slab + smp * 9 * j.plane, t, smp, c, which, v0, v1);
             const double e0 = v0 - mu[0], e1 = v1 - mu[1];
             if (K > 0) {
-                q0.add(a[smp] * e0 * e0);
-                q1.add(a[smp] * e1 * e1);
+                q[0].add(a[smp] * e0 * e0);
+                q[1].add(a[smp] * e1 * e1);
             } else {
-                q0.add(e0 * e0);
-                q1.add(e1 * e1);
+                q[0].add(e0 * e0);
+                q[1].add(e1 * e1);
             }
         }
-        const double qs[2] = {q0.val(), q1.val()};
-        for (int q = 0; q < comps; ++q) {
-            const int64_t o = q * cells + c;
-            if (K > 0) {
-                var_alt[o] = qs[q];
-            } else {
-                mean[o] = mu[q];
-                var[o] = j.S > 1 ? qs[q] / (double)(j.S - 1) : 0.0;
-                var_alt[o] = qs[q] / (double)j.S;
-            }
+    double qs[2];
+    join(q, qs);
+    if (!on || w != 0) return;
+    for (int k = 0; k < comps; ++k) {
+        const int64_t o = k * cells + c;
+        if (K > 0) {
+            var_alt[o] = qs[k];
+        } else {
+            mean[o] = mu[k];
+            var[o] = j.S > 1 ? qs[k] / (double)(j.S - 1) : 0.0;
+            var_alt[o] = qs[k] / (double)j.S;
         }
     }
 }
@@ -588,54 +659,53 @@ __global__ __launch_bounds__(256) void k_field_finish(JobDev j, int64_t t, int w
 // ------------------------------------------------------------------ scalar statistics
 // A scalar QoI (one value per sample): every sum over the samples is split
 // across a workgroup's 256 threads (thread r takes samples r, r + 256, ...
-// in order, a compensated partial each) and the partials are combined in
-// thread order by a compensated sum, so the result does not depend on
-// timing. SC: workgroup k forms c_k (Eq. coef_discrete); then one workgroup
+// in order, a compensated partial each) and the partials are joined in a fixed
+// tree of compensated sums, so the result does not depend on timing (one
+// thread adding up 256 partials took most of these kernels' 8 us). SC: workgroup k forms c_k (Eq. coef_discrete); then one workgroup
 // forms mean = c_0, var = sum_{k>=1} c_k^2 and the quadrature variance. MC:
 // one workgroup forms mean, var (1/(N-1)) and var_alt (1/N).
-__device__ inline double block_nsum(double part, double *red) {
-    red[threadIdx.x] = part;
-    __syncthreads();
-    double r = 0.0;
-    if (threadIdx.x == 0) {
-        NSum acc;
-        for (int i = 0; i < (int)blockDim.x; ++i) acc.add(red[i]);
-        red[0] = acc.val();
+__device__ inline double block_nsum(NSum part, double *red) {
+    wave_join(part);
+    const int w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        red[2 * w] = part.s;
+        red[2 * w + 1] = part.c;
     }
     __syncthreads();
-    r = red[0];
+    NSum acc;
+    for (int i = 0; i < 4; ++i) acc.join(red[2 * i], red[2 * i + 1]);
     __syncthreads();
-    return r;
+    return acc.val();
 }
 
 __global__ __launch_bounds__(256) void k_scalar_coeffs(const double *M, int64_t S, const double *wphi, int K,
                                                        double *coeffs) {
-    __shared__ double red[256];
+    __shared__ double red[8];
     const int k = blockIdx.x;
     NSum acc;
     for (int64_t jx = threadIdx.x; jx < S; jx += blockDim.x) acc.add(wphi[jx * K + k] * M[jx]);
-    const double v = block_nsum(acc.val(), red);
+    const double v = block_nsum(acc, red);
     if (threadIdx.x == 0) coeffs[k] = v;
 }
 
 __global__ __launch_bounds__(256) void k_scalar_finish(const double *M, int64_t S, const double *a, int K,
                                                        const double *coeffs, double *mean, double *var,
                                                        double *var_alt) {
-    __shared__ double red[256];
+    __shared__ double red[8];
     double mu;
     if (K > 0) {
         mu = coeffs[0];
     } else {
         NSum s;
         for (int64_t jx = threadIdx.x; jx < S; jx += blockDim.x) s.add(M[jx]);
-        mu = block_nsum(s.val(), red) / (double)S;
+        mu = block_nsum(s, red) / (double)S;
     }
     NSum q;
     for (int64_t jx = threadIdx.x; jx < S; jx += blockDim.x) {
         const double e = M[jx] - mu;
         q.add(K > 0 ? a[jx] * e * e : e * e);
     }
-    const double qs = block_nsum(q.val(), red);
+    const double qs = block_nsum(q, red);
     if (threadIdx.x == 0) {
         mean[0] = mu;
         if (K > 0) {
@@ -655,23 +725,40 @@ __global__ void k_advance(int64_t *d_t, int64_t n) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *d_t += n;
 }
 
-// out[0] = smallest s < S with qoi[4s + 3] != 0 (non-finite values in sample
-// s), else S. One workgroup of 256: strided scan, then an LDS min-reduction.
-__global__ __launch_bounds__(256) void k_first_bad(const double *qoi, int64_t S, int64_t *out) {
+// The chunks of a sample in order (chunks > 1), and flag[0] = smallest s < S
+// with qoi[4s + 3] != 0 (non-finite values in sample s), else S. One workgroup.
+__global__ __launch_bounds__(256) void k_qoi_join(double ke_norm, int64_t S, int chunks, const double *part,
+                                                  double *qoi, int64_t *flag) {
     __shared__ int64_t red[256];
     int64_t first = S;
-    for (int64_t s = threadIdx.x; s < S; s += blockDim.x)
-        if (qoi[4 * s + 3] != 0.0) {
-            first = s;
-            break;
+    for (int64_t s = threadIdx.x; s < S; s += blockDim.x) {
+        double bad;
+        if (chunks > 1) {
+            NSum ke, fx, fy;
+            bad = 0.0;
+            for (int k = 0; k < chunks; ++k) {
+                const double *q = part + (s * chunks + k) * QOI_PART;
+                ke.join(q[0], q[1]);
+                fx.join(q[2], q[3]);
+                fy.join(q[4], q[5]);
+                bad += q[6];
+            }
+            qoi[4 * s] = ke.val() * ke_norm;
+            qoi[4 * s + 1] = fx.val();
+            qoi[4 * s + 2] = fy.val();
+            qoi[4 * s + 3] = bad;
+        } else {
+            bad = qoi[4 * s + 3];
         }
+        if (bad != 0.0 && s < first) first = s;
+    }
     red[threadIdx.x] = first;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) red[threadIdx.x] = min(red[threadIdx.x], red[threadIdx.x + w]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[0] = red[0];
+    if (threadIdx.x == 0) flag[0] = red[0];
 }
 
 // which: UQ_QOI_KE -> KE; UQ_QOI_CD / UQ_QOI_CL -> 2 F/(u_peak^2 D) with the
@@ -1000,14 +1087,26 @@ hipError_t launch_select_scalar(const JobDev &j, const double *qoi, int which, d
     return hipGetLastError();
 }
 
-hipError_t launch_first_bad(const double *qoi, int64_t S, int64_t *out, hipStream_t s) {
-    k_first_bad<<<1, 256, 0, s>>>(qoi, S, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_qoi_scalars(const JobDev &j, int64_t t, double *out, hipStream_t s) {
-    dim3 grid((unsigned)j.S);
-    UQ_DISPATCH(k_qoi, t & 1, grid, 256, s, j, t, out);
+// Chunks per sample of k_qoi: about 8 workgroups per CU in all, 4 nodes or
+// more per thread. Their sums go to the slab that does not hold the state (AB:
+// the next step overwrites all of it that is ever read).
+hipError_t launch_qoi_scalars(const JobDev &j, int64_t t, double *out, int64_t *flag, hipStream_t s) {
+    const int64_t cells = (int64_t)j.nx * j.ny;
+    const int64_t slab2 = j.plane * (j.prec == UQ_FP64 ? 72 : (j.prec == UQ_FP32 ? 36 : 18));  // bytes a sample
+    int64_t chunks = 1;
+    double *part = nullptr;
+    if (j.layout == UQ_LAYOUT_AB) {
+        part = (double *)((t & 1) ? j.f : j.f2);
+        chunks = std::min<int64_t>(std::min<int64_t>(2048 / j.S, (cells + 1023) / 1024), slab2 / (QOI_PART * 8));
+        chunks = std::max<int64_t>(1, chunks);
+    }
+    const int per = (int)((cells + chunks - 1) / chunks);
+    const unsigned gy = (unsigned)std::min<int64_t>(j.S, 32768);
+    dim3 grid((unsigned)chunks, gy, (unsigned)((j.S + gy - 1) / gy));
+    UQ_DISPATCH(k_qoi, t & 1, grid, 256, s, j, t, per, part, out);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    k_qoi_join<<<1, 256, 0, s>>>(j.ke_norm, j.S, (int)chunks, part, out, flag);
     return hipGetLastError();
 }
 
@@ -1029,8 +1128,11 @@ hipError_t launch_field_moments(const JobDev &j, int64_t t, int qoi, const doubl
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    dim3 grid2((unsigned)std::min<int64_t>((cells + 255) / 256, 65535));
-    UQ_DISPATCH(k_field_finish, t & 1, grid2, 256, s, j, t, which, a, K, coeffs, mean, var, var_alt);
+    // waves per 64 nodes: 8 samples or more each, and no more than give every
+    // CU 32 waves (large lattices have enough nodes)
+    const int64_t blocks = (cells + 63) / 64;
+    const int64_t G = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(FF_MAX_G, (j.S + 7) / 8), (256 * 32 + blocks - 1) / blocks));
+    UQ_DISPATCH(k_field_finish, t & 1, dim3((unsigned)blocks), 64 * (unsigned)G, s, j, t, which, a, K, coeffs, mean, var, var_alt);
     return hipGetLastError();
 }
 

@@ -444,11 +444,9 @@ extern "C" uq_status uq_sync(uq_job *j) {
 
 namespace uqi {
 
-// Per-sample scalar QoIs into b.qoi, and UQ_EUNSTABLE if any sample holds a
-// non-finite value. Blocking (one flag read).
+// Reads the flag of launch_qoi_scalars, the last thing on the stream:
+// UQ_EUNSTABLE if any sample holds a non-finite value. Blocking.
 uq_status Job::check_finite(const StatBufs &b) {
-    UQ_HIP_TRY(launch_qoi_scalars(jd, t, b.qoi, stream));
-    UQ_HIP_TRY(launch_first_bad(b.qoi, S, b.flag, stream));
     int64_t bad = S;
     UQ_HIP_TRY(hipMemcpyAsync(&bad, b.flag, sizeof(int64_t), hipMemcpyDeviceToHost, stream));
     UQ_HIP_TRY(hipStreamSynchronize(stream));
@@ -457,16 +455,16 @@ uq_status Job::check_finite(const StatBufs &b) {
     return UQ_OK;
 }
 
-// Per-sample values of one QoI in the buffers b. Returns the device pointer,
-// number of values per sample and the row stride. Blocking (one flag read).
+// Per-sample values of one QoI in the buffers b, with the device pointer,
+// number of values per sample and row stride. The caller waits with
+// check_finite after its own work: a non-finite sample is reported then.
 uq_status Job::sample_values_in(const StatBufs &b, int qoi, const double **M, int64_t *n_out, int64_t *ld) {
     const uq_problem &P = p;
     const int64_t cells = (int64_t)P.nx * P.ny;
     if (qoi_width(P, qoi) == 0) return fail(UQ_EINVAL, "unknown QoI");
     if ((qoi == UQ_QOI_CD || qoi == UQ_QOI_CL) && (P.geometry != UQ_GEOM_CHANNEL || (P.D <= 0 && P.cyl_bc != UQ_CYL_BOUZIDI)))
         return fail(UQ_EINVAL, "drag/lift need a channel with a cylinder");
-    uq_status st = check_finite(b);
-    if (st != UQ_OK) return st;
+    UQ_HIP_TRY(launch_qoi_scalars(jd, t, b.qoi, b.flag, stream));
     if (qoi_width(P, qoi) == 1) {
         UQ_HIP_TRY(launch_select_scalar(jd, b.qoi, qoi, b.M, stream));
         *M = b.M;
@@ -486,7 +484,8 @@ uq_status Job::sample_values(int qoi, const double **M, int64_t *n_out, int64_t 
     StatBufs b;
     uq_status st = own_stat_bufs(qoi, true, &b);
     if (st != UQ_OK) return st;
-    return sample_values_in(b, qoi, M, n_out, ld);
+    st = sample_values_in(b, qoi, M, n_out, ld);
+    return st == UQ_OK ? check_finite(b) : st;
 }
 
 // Scalar QoIs: per-sample values, then the sums over samples spread across a
@@ -498,27 +497,40 @@ uq_status Job::moments_in(const StatBufs &b, int qoi, uq_moments_out *out) {
     if (st != UQ_OK) return st;
     double *d_mean = b.out, *d_var = b.out + n, *d_alt = b.out + 2 * n, *d_coef = b.out + 3 * n;
     if (n == 1) {
+        // everything is enqueued before the one wait; the results (mean, var,
+        // var_alt, c_k side by side) stay here until the check has passed
         const double *M;
         int64_t n1, ld;
         st = sample_values_in(b, qoi, &M, &n1, &ld);
         if (st != UQ_OK) return st;
         UQ_HIP_TRY(launch_scalar_moments(M, S, d_wphi, d_a, K, d_coef, d_mean, d_var, d_alt, stream));
-    } else {
-        StatBufs scalars = b;
-        scalars.fields = nullptr;
-        st = check_finite(scalars);
+        std::vector<double> h((size_t)(3 + K));
+        UQ_HIP_TRY(hipMemcpyAsync(h.data(), b.out, sizeof(double) * h.size(), hipMemcpyDeviceToHost, stream));
+        st = check_finite(b);
         if (st != UQ_OK) return st;
+        out->n_out = n;
+        out->K = K;
+        out->d = rule.d;
+        if (out->mean) out->mean[0] = h[0];
+        if (out->var) out->var[0] = h[1];
+        if (out->var_alt) out->var_alt[0] = h[2];
+        if (out->coeffs && K > 0) std::memcpy(out->coeffs, h.data() + 3, sizeof(double) * K);
+    } else {
+        UQ_HIP_TRY(launch_qoi_scalars(jd, t, b.qoi, b.flag, stream));
         UQ_HIP_TRY(launch_field_moments(jd, t, qoi, d_wphi, d_a, K, d_coef, d_mean, d_var, d_alt, stream));
+        st = check_finite(b);
+        if (st != UQ_OK) return st;
+        out->n_out = n;
+        out->K = K;
+        out->d = rule.d;
+        const size_t bytes = sizeof(double) * n;
+        if (out->mean) UQ_HIP_TRY(hipMemcpyAsync(out->mean, d_mean, bytes, hipMemcpyDeviceToHost, stream));
+        if (out->var) UQ_HIP_TRY(hipMemcpyAsync(out->var, d_var, bytes, hipMemcpyDeviceToHost, stream));
+        if (out->var_alt) UQ_HIP_TRY(hipMemcpyAsync(out->var_alt, d_alt, bytes, hipMemcpyDeviceToHost, stream));
+        if (out->coeffs && K > 0)
+            UQ_HIP_TRY(hipMemcpyAsync(out->coeffs, d_coef, bytes * K, hipMemcpyDeviceToHost, stream));
+        UQ_HIP_TRY(hipStreamSynchronize(stream));
     }
-    out->n_out = n;
-    out->K = K;
-    out->d = rule.d;
-    if (out->mean) UQ_HIP_TRY(hipMemcpyAsync(out->mean, d_mean, sizeof(double) * n, hipMemcpyDeviceToHost, stream));
-    if (out->var) UQ_HIP_TRY(hipMemcpyAsync(out->var, d_var, sizeof(double) * n, hipMemcpyDeviceToHost, stream));
-    if (out->var_alt) UQ_HIP_TRY(hipMemcpyAsync(out->var_alt, d_alt, sizeof(double) * n, hipMemcpyDeviceToHost, stream));
-    if (out->coeffs && K > 0)
-        UQ_HIP_TRY(hipMemcpyAsync(out->coeffs, d_coef, sizeof(double) * n * K, hipMemcpyDeviceToHost, stream));
-    UQ_HIP_TRY(hipStreamSynchronize(stream));
     if (out->alpha && K > 0) std::memcpy(out->alpha, rule.alpha.data(), sizeof(int32_t) * rule.alpha.size());
     return UQ_OK;
 }
