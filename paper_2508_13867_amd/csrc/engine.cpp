@@ -127,6 +127,16 @@ StepShape choose_shape(const uq_problem &p, int64_t S, bool pipelines) {
         if (v && (v[0] == 'a' || v[0] == 'A') && (v[1] == 'b' || v[1] == 'B')) s.layout = UQ_LAYOUT_AB;
     }
     if (needs_ab(p)) s.layout = UQ_LAYOUT_AB;
+    // Stores that bypass the caches pay where two slabs do not fit the 256 MB
+    // cache beside HBM; where they do, the next step reads them from it. The
+    // paper's 440 x 80 cylinder, us per step with and without: FP64 x 11 (57
+    // MB) 19.8, 14.9; FP32 x 32 (83 MB) 23.8, 20.4; FP64 x 32 (165 MB) 37.2,
+    // 33.7; FP32 x 100 (258 MB) 63.0, 64.4; FP64 x 100 (516 MB) 105, 121.
+    const char *nt = std::getenv("UQ_NT_STORE");
+    if (s.layout == UQ_LAYOUT_AB && !(nt && *nt)) {
+        const int64_t slab = S * 9 * (p.ny * row_pitch(p.nx) + s.pad) * storage_bytes(p.precision);
+        s.nt = 2 * slab > ((int64_t)200 << 20);
+    }
     return s;
 }
 
@@ -203,7 +213,7 @@ hipError_t Job::enqueue_steps(int k0, int64_t n) {
         }
     }
     for (; k < n && e == hipSuccess; ++k) {
-        e = launch_step(jd, d_t, (int)(k0 + k), (int)((t + k0 + k) & 1), shape, stream, &side);
+        e = launch_step(jd, d_t, (int)(k0 + k), (int)((t + k0 + k) & 1), shape, stream);
         ++enqueued;
     }
     return e;
@@ -216,7 +226,7 @@ uq_status Job::advance(int64_t steps) {
     if (const int N = fused_n()) L = L / (2 * N) * (2 * N);
     if (use_graph && L >= 2 && steps >= L + 1) {
         if (t & 1) {
-            UQ_HIP_TRY(launch_step(jd, d_t, 0, 1, shape, stream, &side));
+            UQ_HIP_TRY(launch_step(jd, d_t, 0, 1, shape, stream));
             ++launches;
             UQ_HIP_TRY(launch_advance(d_t, 1, stream));
             t += 1;
@@ -262,12 +272,8 @@ Job::~Job() {
     if (stream) (void)hipStreamSynchronize(stream);
     release_graph();
     dfree_all();
-    if (side.stream) (void)hipStreamSynchronize(side.stream);
     if (ev_in) (void)hipEventDestroy(ev_in);
     if (ev_out) (void)hipEventDestroy(ev_out);
-    if (side.fork) (void)hipEventDestroy(side.fork);
-    if (side.join) (void)hipEventDestroy(side.join);
-    if (side.stream) (void)hipStreamDestroy(side.stream);
     if (stream) (void)hipStreamDestroy(stream);
 }
 

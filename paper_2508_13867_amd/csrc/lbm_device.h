@@ -427,7 +427,7 @@ __device__ inline void fd_rebuild(C f[9], double rho, double ux, double dxux, do
 }
 
 // the whole reconstruction for one node, neighbours gathered here (QoI and
-// export kernels; the step uses k_fd_columns, which shares them in LDS)
+// export kernels; the step shares them in LDS, fd_column_chunk)
 template <int P>
 __device__ inline void fd_column(const JobDev &j, const typename Prec<P>::T *base, const Site &s, int64_t t,
                                  double u_peak, double omega, typename Prec<P>::C f[9]) {

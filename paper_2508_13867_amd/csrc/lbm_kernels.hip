@@ -44,9 +44,9 @@ __device__ inline void tile_update(const JobDev &j, int64_t t, int64_t smp, int 
         m[r] = 0;
         if (CHANNEL && live[r]) {
             m[r] = j.mask[(int64_t)y * j.pitch + x];
-            // solid nodes, and the boundary nodes that k_qlinks and
-            // k_fd_columns update (interpolated links, finite-difference
-            // open columns), are not stepped here
+            // solid nodes, and the boundary nodes that k_step_interp updates
+            // apart (interpolated links, finite-difference open columns),
+            // are not stepped here
             live[r] = !(m[r] & (M_SOLID | M_SPECIAL));
         }
         if (live[r]) gather<P, CHANNEL, MODE, false, false>(j, src, site(j, x, y), m[r], t, u_peak, omega_d, f[r]);
@@ -75,101 +75,162 @@ __global__ __launch_bounds__(256) void k_step(JobDev j, const int64_t *d_t, int 
     }
 }
 
-// Boundary nodes of jobs with interpolated boundaries (AB layout), stepped
-// apart from k_step so that the bulk kernel keeps its registers and
-// occupancy. Both kernels below read only the source slab and write only
-// their own nodes of the destination slab, so they and k_step of the same
-// step are independent.
+// Boundary nodes of jobs with interpolated boundaries (AB layout). Both items
+// below read only the source slab and write only their own nodes of the
+// destination slab, so they and the bulk tiles of the same step are
+// independent.
 //
-// Nodes with interpolated cylinder links (listed in j.special), one thread
-// per (node, sample): gather with the interpolation, collide, store.
-template <int P, int PARITY>
-__global__ __launch_bounds__(64) void k_qlinks(JobDev j, const int64_t *d_t, int k) {
+// A node with interpolated cylinder links (listed in j.special) of one
+// sample. Every value that any of its links may want (its streamed and own
+// populations, those of the nodes behind, the link fractions) is loaded before
+// the first is used: with the loads under each link's branch a step of the
+// list was a chain of some ten memory latencies (12.7 us for 80 nodes).
+template <int P>
+__device__ inline void qlink_node(const JobDev &j, const void *src_all, void *dst_all, int64_t t, int64_t smp, int e) {
     using PR = Prec<P>;
     using C = typename PR::C;
     using T = typename PR::T;
-    const int64_t t = *d_t + k;
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= j.n_special) return;
-    const int64_t node = j.special[e];
-    const int y = (int)(node / j.pitch), x = (int)(node - (int64_t)y * j.pitch);
+    const int node = j.special[e];
+    const int y = node / (int)j.pitch, x = node - y * (int)j.pitch;
     const uint32_t m = j.mask[node];
-    const T *src_all = (const T *)(PARITY ? j.f2 : j.f);
-    T *dst_all = (T *)(PARITY ? j.f : j.f2);
-    const Site st = site(j, x, y);
-    for (int64_t smp = blockIdx.y; smp < j.S; smp += gridDim.y) {
-        const SampleDev &sd = j.smp[smp];
-        C f[9], drho, ux, uy;
-        gather<P, true, AB_PULL, false, true>(j, src_all + smp * 9 * j.plane, st, m, t, sd.u_peak, sd.omega, f);
-        bgk(f, (C)sd.omega, drho, ux, uy);
-        scatter<P, true, AB_PULL, false>(j, dst_all + smp * 9 * j.plane, st, m, f);
+    const Site s = site(j, x, y);
+    const T *base = (const T *)src_all + smp * 9 * j.plane;
+    const SampleDev &sd = j.smp[smp];
+    const float inv = j.inv_scale;
+    C f[9], own[9], behind[9];
+    double q[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+        f[i] = PR::ld(base + i * j.plane + (int64_t)sy_of(s, -CYd[i]) * j.pitch + sx_of(s, -CXd[i]), inv);
+        own[i] = PR::ld(base + i * j.plane + node, inv);
+        behind[i] = PR::ld(base + OPPd[i] * j.plane + (int64_t)sy_of(s, CYd[i]) * j.pitch + sx_of(s, CXd[i]), inv);
+        q[i] = j.q[(int64_t)i * j.ny * j.pitch + node];
     }
+#pragma unroll
+    for (int i = 1; i < 9; ++i) {
+        const bool bb = (m >> (M_BB + i)) & 1u;
+        const C fk = own[OPPd[i]];
+        C v = fk;  // a half-way link (channel wall)
+        if (q[i] > 0.0) {
+            if (q[i] >= 0.5) {
+                const double a = 1.0 / (2.0 * q[i]);
+                v = (C)a * fk + (C)(1.0 - a) * own[i];
+            } else {
+                v = (C)(2.0 * q[i]) * fk + (C)(1.0 - 2.0 * q[i]) * behind[i];
+            }
+        }
+        f[i] = bb ? v : f[i];
+    }
+    // beyond an open column, as in the gather
+    if (m & (0x1FFu << M_OPEN)) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) f[i] = ((m >> (M_OPEN + i)) & 1u) ? C(0) : f[i];
+        if (t > 0 && j.xbc != UQ_XBC_INTERP) zou_he(f, j, x, y, t, sd.u_peak);
+    }
+    C drho, ux, uy;
+    bgk(f, (C)sd.omega, drho, ux, uy);
+    scatter<P, true, AB_PULL, false>(j, (T *)dst_all + smp * 9 * j.plane, s, m, f);
 }
 
-// The two open columns of a finite-difference inlet/outlet. One workgroup
-// per (column, chunk of FD_ROWS rows, sample); its threads gather, one node
-// each, the column node and the two nodes next to it into the fluid, for the
-// chunk's rows plus two halo rows on each side, and share the velocities
-// through LDS; the column threads then rebuild, collide and store.
+// A chunk of FD_ROWS rows of an open column (inlet chunks first) of a
+// finite-difference inlet/outlet, of one sample. A workgroup's threads
+// gather, one node each, the column node and the two nodes next to it into the
+// fluid, for the chunk's rows plus two halo rows on each side, and share the
+// velocities through LDS; the column threads then rebuild, collide and store.
 constexpr int FD_RB = 85, FD_HALO = 2, FD_ROWS = FD_RB - 2 * FD_HALO, FD_BLOCK = 256;
+struct FdLds {
+    double ub[FD_RB], u1x[FD_RB], u1y[FD_RB], u2x[FD_RB], u2y[FD_RB];
+};
 
-template <int P, int PARITY>
-__global__ __launch_bounds__(FD_BLOCK) void k_fd_columns(JobDev j, const int64_t *d_t, int k) {
+template <int P>
+__device__ inline void fd_column_chunk(const JobDev &j, const void *src_all, void *dst_all, int64_t t, int64_t smp,
+                                       int item, FdLds &l) {
     using PR = Prec<P>;
     using C = typename PR::C;
     using T = typename PR::T;
-    __shared__ double ub[FD_RB], u1x[FD_RB], u1y[FD_RB], u2x[FD_RB], u2y[FD_RB];
-    const int64_t t = *d_t + k;
     const int chunks = (j.ny + FD_ROWS - 1) / FD_ROWS;
-    const bool inlet = (int)blockIdx.x < chunks;
-    const int chunk = inlet ? (int)blockIdx.x : (int)blockIdx.x - chunks;
-    const int tid = threadIdx.x;
+    const bool inlet = item < chunks;
+    const int chunk = inlet ? item : item - chunks;
+    const int tid = (int)(threadIdx.y * blockDim.x + threadIdx.x);
     const int c = tid / FD_RB, r = tid - c * FD_RB;  // c: 0 the column, 1 and 2 into the fluid
     const int x = inlet ? c : j.nx - 1 - c;
     const int y = chunk * FD_ROWS - FD_HALO + r;
     const bool valid = c < 3 && y >= 0 && y < j.ny;
     const bool own = valid && c == 0 && r >= FD_HALO && r < FD_RB - FD_HALO;
     const uint32_t m = valid ? j.mask[(int64_t)y * j.pitch + x] : 0u;
-    const T *src_all = (const T *)(PARITY ? j.f2 : j.f);
-    T *dst_all = (T *)(PARITY ? j.f : j.f2);
-    for (int64_t smp = blockIdx.y; smp < j.S; smp += gridDim.y) {
-        const SampleDev &sd = j.smp[smp];
-        const T *src = src_all + smp * 9 * j.plane;
-        C f[9];
-        double rho = 1.0, ux = 0.0;
-        if (valid) {
-            const Site st = site(j, x, y);
-            if (c == 0) {
-                gather<P, true, AB_PULL, false, false>(j, src, st, m, t, sd.u_peak, sd.omega, f);
-                fd_state(j, f, inlet, y, t, sd.u_peak, rho, ux);
-                ub[r] = ux;
-            } else {
-                C drho, gx, gy;
-                gather<P, true, AB_PULL, false, true>(j, src, st, m, t, sd.u_peak, sd.omega, f);
-                moments(f, drho, gx, gy);
-                if (c == 1) {
-                    u1x[r] = (double)gx;
-                    u1y[r] = (double)gy;
-                } else {
-                    u2x[r] = (double)gx;
-                    u2y[r] = (double)gy;
-                }
-            }
-        }
-        __syncthreads();
-        if (own) {
-            if (t > 0) {  // the state at t = 0 is the rest state as gathered
-                const double sdx = inlet ? 1.0 : -1.0;
-                const double dyux = fd_dy(y, j.ny, ub[r - 2], ub[r - 1], ux, ub[r + 1], ub[r + 2]);
-                const double dxux = sdx * (-3.0 * ux + 4.0 * u1x[r] - u2x[r]) * 0.5;
-                const double dxuy = sdx * (-3.0 * 0.0 + 4.0 * u1y[r] - u2y[r]) * 0.5;
-                fd_rebuild(f, rho, ux, dxux, dxuy, dyux, sd.omega);
-            }
+    const SampleDev &sd = j.smp[smp];
+    const T *src = (const T *)src_all + smp * 9 * j.plane;
+    C f[9];
+    double rho = 1.0, ux = 0.0;
+    if (valid) {
+        const Site st = site(j, x, y);
+        if (c == 0) {
+            gather<P, true, AB_PULL, false, false>(j, src, st, m, t, sd.u_peak, sd.omega, f);
+            fd_state(j, f, inlet, y, t, sd.u_peak, rho, ux);
+            l.ub[r] = ux;
+        } else {
             C drho, gx, gy;
-            bgk(f, (C)sd.omega, drho, gx, gy);
-            scatter<P, true, AB_PULL, false>(j, dst_all + smp * 9 * j.plane, site(j, x, y), m, f);
+            gather<P, true, AB_PULL, false, true>(j, src, st, m, t, sd.u_peak, sd.omega, f);
+            moments(f, drho, gx, gy);
+            if (c == 1) {
+                l.u1x[r] = (double)gx;
+                l.u1y[r] = (double)gy;
+            } else {
+                l.u2x[r] = (double)gx;
+                l.u2y[r] = (double)gy;
+            }
         }
-        __syncthreads();  // the LDS rows are reused by the next sample
+    }
+    __syncthreads();
+    if (own) {
+        if (t > 0) {  // the state at t = 0 is the rest state as gathered
+            const double sdx = inlet ? 1.0 : -1.0;
+            const double dyux = fd_dy(y, j.ny, l.ub[r - 2], l.ub[r - 1], ux, l.ub[r + 1], l.ub[r + 2]);
+            const double dxux = sdx * (-3.0 * ux + 4.0 * l.u1x[r] - l.u2x[r]) * 0.5;
+            const double dxuy = sdx * (-3.0 * 0.0 + 4.0 * l.u1y[r] - l.u2y[r]) * 0.5;
+            fd_rebuild(f, rho, ux, dxux, dxuy, dyux, sd.omega);
+        }
+        C drho, gx, gy;
+        bgk(f, (C)sd.omega, drho, gx, gy);
+        scatter<P, true, AB_PULL, false>(j, (T *)dst_all + smp * 9 * j.plane, site(j, x, y), m, f);
+    }
+}
+
+// One step of a job with interpolated boundaries in one launch: workgroups
+// [0, nfd) take the open-column chunks, [nfd, nb) the cylinder's nodes (one
+// per thread, samples side by side), the rest the bulk tiles of k_step. The
+// boundary work, the longest chain of loads, starts first; handed out among
+// the tiles, or sample by sample with them, it took longer (11 samples of 440 x
+// 80: 11.7 us per step first, 15.1 and 14.5 so). As three kernels, two of them
+// on a side stream, the step took 28.5 us, half of it the host's: a graph node
+// per kernel and a fork and a join per step. 1000 samples: 618 us, as before
+// (held to 8 waves per SIMD; 636 at the 7 the compiler takes otherwise).
+template <int P, int PARITY, bool NT>
+__global__ __launch_bounds__(FD_BLOCK, P == UQ_FP64 ? 4 : 8) void k_step_interp(JobDev j, const int64_t *d_t, int k,
+                                                                               int fd_items, int nfd, int nb,
+                                                                               int tiles_x, int tiles_y,
+                                                                               int64_t ntiles) {
+    __shared__ FdLds lds;
+    const int64_t t = *d_t + k;
+    const void *src = PARITY ? j.f2 : j.f;
+    void *dst = PARITY ? j.f : j.f2;
+    const int g = blockIdx.x;
+    if (g < nb) {
+        if (g < nfd) {
+            fd_column_chunk<P>(j, src, dst, t, g / fd_items, g % fd_items, lds);
+        } else {
+            const int64_t w = (int64_t)(g - nfd) * FD_BLOCK + threadIdx.y * blockDim.x + threadIdx.x;
+            const int64_t smp = w / j.n_special;
+            if (smp < j.S) qlink_node<P>(j, src, dst, t, smp, (int)(w - smp * j.n_special));
+        }
+        return;
+    }
+    const int64_t per_sample = (int64_t)tiles_x * tiles_y, G = (int64_t)gridDim.x - nb;
+    for (int64_t tile = xcd_logical(g - nb, G); tile < ntiles; tile += G) {
+        const int64_t smp = tile / per_sample;
+        const int64_t rem = tile - smp * per_sample;
+        const int ty = (int)(rem / tiles_x), tx = (int)(rem - (int64_t)ty * tiles_x);
+        tile_update<P, true, PARITY, 1, UQ_LAYOUT_AB, NT>(j, t, smp, tx, ty);
     }
 }
 // The same address as a pointer into global memory. A pointer loaded from a
@@ -866,9 +927,25 @@ static void step_cpt(const JobDev &j, const int64_t *d_t, int k, int parity, boo
     }
 }
 
+template <int P>
+static void step_interp_p(const JobDev &j, const int64_t *d_t, int k, bool odd, bool nt, int64_t tile_groups,
+                          dim3 block, hipStream_t s, int tiles_x, int tiles_y) {
+    const int64_t ntiles = (int64_t)j.S * tiles_x * tiles_y;
+    const int fd_items = j.xbc == UQ_XBC_INTERP ? 2 * ((j.ny + FD_ROWS - 1) / FD_ROWS) : 0;
+    const int nfd = fd_items * j.S;
+    const int nb = nfd + (int)(((int64_t)j.n_special * j.S + FD_BLOCK - 1) / FD_BLOCK);
+    const int64_t G = nb + std::min<int64_t>(tile_groups, 0x3fffffff);
+#define UQ_STEP(PAR, NT_)                                                                                             \
+    k_step_interp<P, PAR, NT_><<<(unsigned)G, block, 0, s>>>(j, d_t, k, fd_items, nfd, nb, tiles_x, tiles_y, ntiles)
+    if (nt) { if (odd) UQ_STEP(1, true); else UQ_STEP(0, true); }
+    else { if (odd) UQ_STEP(1, false); else UQ_STEP(0, false); }
+#undef UQ_STEP
+}
+
 hipError_t launch_step(const JobDev &j, const int64_t *d_t, int k, int parity, const StepShape &shape,
-                       hipStream_t s_main, const SideStream *side) {
-    const int cpt = shape.cpt <= 1 ? 1 : 2;
+                       hipStream_t s) {
+    const bool interp = j.geom == 1 && j.layout == UQ_LAYOUT_AB && (j.xbc == UQ_XBC_INTERP || j.n_special > 0);
+    const int cpt = shape.cpt <= 1 || interp ? 1 : 2;
     const int bx = shape.bx == 128 || shape.bx == 256 ? shape.bx : BX;
     const int by = 256 / bx;
     const int tiles_x = (j.nx + bx - 1) / bx;
@@ -878,61 +955,21 @@ hipError_t launch_step(const JobDev &j, const int64_t *d_t, int k, int parity, c
     if (shape.persistent > 0) G = std::min<int64_t>(ntiles, (int64_t)256 * shape.persistent);
     if (G > 0x7fffffff) G = 0x7fffffff;
     dim3 block(bx, by);
-    dim3 grid((unsigned)G);
     const bool nt = shape.nt != 0;
-    const bool odd = parity & 1;
-    const unsigned gs = (unsigned)std::min<int64_t>(j.S, 65535);
-    const bool fd_cols = j.geom == 1 && j.xbc == UQ_XBC_INTERP && j.layout == UQ_LAYOUT_AB;
-    // boundary-node kernels: on the side stream when there is one
-    hipStream_t s = s_main;
-    if ((j.n_special > 0 || fd_cols) && side && side->stream) {
-        hipError_t e = hipEventRecord(side->fork, s_main);
-        if (e == hipSuccess) e = hipStreamWaitEvent(side->stream, side->fork, 0);
-        if (e != hipSuccess) return e;
-        s = side->stream;
-    }
-    if (j.n_special > 0) {
-        dim3 og((unsigned)((j.n_special + 63) / 64), gs);
-#define UQ_QL(PP)                                                        \
-    do {                                                                 \
-        if (odd) k_qlinks<PP, 1><<<og, 64, 0, s>>>(j, d_t, k);           \
-        else k_qlinks<PP, 0><<<og, 64, 0, s>>>(j, d_t, k);               \
-    } while (0)
+    if (interp) {
+        const bool odd = parity & 1;
         switch (j.prec) {
-            case UQ_FP64: UQ_QL(UQ_FP64); break;
-            case UQ_FP32: UQ_QL(UQ_FP32); break;
-            case UQ_FP16S: UQ_QL(UQ_FP16S); break;
-            default: UQ_QL(UQ_BF16S); break;
+            case UQ_FP64: step_interp_p<UQ_FP64>(j, d_t, k, odd, nt, G, block, s, tiles_x, tiles_y); break;
+            case UQ_FP32: step_interp_p<UQ_FP32>(j, d_t, k, odd, nt, G, block, s, tiles_x, tiles_y); break;
+            case UQ_FP16S: step_interp_p<UQ_FP16S>(j, d_t, k, odd, nt, G, block, s, tiles_x, tiles_y); break;
+            default: step_interp_p<UQ_BF16S>(j, d_t, k, odd, nt, G, block, s, tiles_x, tiles_y); break;
         }
-#undef UQ_QL
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+        return hipGetLastError();
     }
-    if (fd_cols) {
-        dim3 fg((unsigned)(2 * ((j.ny + FD_ROWS - 1) / FD_ROWS)), gs);
-#define UQ_FDC(PP)                                                                  \
-    do {                                                                            \
-        if (odd) k_fd_columns<PP, 1><<<fg, FD_BLOCK, 0, s>>>(j, d_t, k);             \
-        else k_fd_columns<PP, 0><<<fg, FD_BLOCK, 0, s>>>(j, d_t, k);                 \
-    } while (0)
-        switch (j.prec) {
-            case UQ_FP64: UQ_FDC(UQ_FP64); break;
-            case UQ_FP32: UQ_FDC(UQ_FP32); break;
-            case UQ_FP16S: UQ_FDC(UQ_FP16S); break;
-            default: UQ_FDC(UQ_BF16S); break;
-        }
-#undef UQ_FDC
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (cpt == 1) step_cpt<1>(j, d_t, k, parity & 1, nt, grid, block, s_main, tiles_x, tiles_y, ntiles);
-    else step_cpt<2>(j, d_t, k, parity & 1, nt, grid, block, s_main, tiles_x, tiles_y, ntiles);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess && s != s_main) {
-        e = hipEventRecord(side->join, s);
-        if (e == hipSuccess) e = hipStreamWaitEvent(s_main, side->join, 0);
-    }
-    return e;
+    dim3 grid((unsigned)G);
+    if (cpt == 1) step_cpt<1>(j, d_t, k, parity & 1, nt, grid, block, s, tiles_x, tiles_y, ntiles);
+    else step_cpt<2>(j, d_t, k, parity & 1, nt, grid, block, s, tiles_x, tiles_y, ntiles);
+    return hipGetLastError();
 }
 
 hipError_t launch_step_multi(const MultiJob *jobs, int njobs, int64_t ntiles, int k, int prec, hipStream_t s) {

@@ -68,8 +68,8 @@ struct alignas(64) SampleDev {
 //  bits 21..29 : the link x -> x + c_i enters the cylinder (force links)
 //  bit  30     : some bounce-back link of the node is interpolated (the link
 //                fractions are in JobDev::q)
-//  bit  31     : the node is stepped by a boundary-node kernel (interpolated
-//                links, finite-difference open columns), not the bulk kernel
+//  bit  31     : the node is stepped apart from the bulk (interpolated links,
+//                finite-difference open columns)
 enum : uint32_t {
     M_BB = 0,
     M_OPEN = 9,
@@ -151,15 +151,8 @@ struct StepShape {
 // one stream-collide step for all samples at time t = *d_t + k; `parity`
 // must equal t & 1 (the host keeps a mirror of t)
 hipError_t launch_init(const JobDev &j, hipStream_t s);
-// A second stream for the boundary-node kernels (interpolated links,
-// finite-difference columns): they run beside k_step of the same step,
-// forked from and joined back into the main stream with the two events.
-struct SideStream {
-    hipStream_t stream = nullptr;
-    hipEvent_t fork = nullptr, join = nullptr;
-};
 hipError_t launch_step(const JobDev &j, const int64_t *d_t, int k, int parity, const StepShape &shape,
-                       hipStream_t s, const SideStream *side = nullptr);
+                       hipStream_t s);
 // n = 2..4 fused steps of a periodic AB job in one launch: the state is
 // read from slab f2 if src2 else f and n steps later written to the other
 // slab (the host keeps the slab of each step's state; see Job::enqueue_steps)
