@@ -26,7 +26,7 @@ static int env_int(const char *name, int dflt) {
 // 32, 64, 128, 256 rows took 50.2, 44.1, 44.7, 52.4 us per step, in the
 // ratios of this count). Items that have a CU to themselves run faster: a
 // round that gives each CU at most one counts 0.6.
-int chunk_rows(int ny, int64_t items, int fill, int per_cu) {
+int chunk_rows(int ny, int64_t items, int fill, int per_cu, double *cost_out) {
     const int64_t slots = (int64_t)256 * per_cu;
     double best = 0.0;
     int rows = ny;
@@ -41,6 +41,7 @@ int chunk_rows(int ny, int64_t items, int fill, int per_cu) {
             rows = H;
         }
     }
+    if (cost_out) *cost_out = best;
     return std::max(8, rows);
 }
 
@@ -49,11 +50,33 @@ int chunk_rows(int ny, int64_t items, int fill, int per_cu) {
 // with one column per lane (28 waves per CU) and 101-111 with two (16),
 // double precision 110 (16) and 188-197 (8); the channel's 90-98 (20), 135-145
 // (12), 147-193 (8) and 235-247 (8).
-static int pipeline_per_cu(int prec, int n, int rows, int K, int M) {
+int pipeline_per_cu(int prec, int n, int rows, int K, int M) {
     const bool ch = rows == RING_ROWS_CH, dbl = prec == UQ_FP64;
     const int waves = M == 1 ? (dbl ? (ch ? 8 : 16) : (ch ? 20 : 28)) : (dbl ? 8 : (ch ? 12 : 16));
     const int64_t lds = (int64_t)(n - 1) * rows * ring_cols(rows, K, M) * (dbl ? 8 : 4);
     return (int)std::max<int64_t>(1, std::min<int64_t>(waves / (n * K), 160 * 1024 / lds));
+}
+
+// A channel's pipeline: strips at the most steps per launch, or 4 steps over
+// whole rows where single precision's rings hold them and the count of rounds
+// x row steps per step says so (a row step of either takes about 1.1 us). Us
+// per step, strips and whole rows: FP32 220 x 41 x 512 samples 31.9, 28.7; 308
+// x 57 x 64 10.5, 8.8; 440 x 82 x 64 13.9, 14.3 (3 steps); x 8 5.0, 6.9; 660 x
+// 123 x 32 20.0, 21.8 (2 steps); 880 x 164 x 32 25.2, one step per launch 53.9;
+// FP64 220 x 41 x 64 8.0, 8.5 (3 steps); 440 x 82 x 64 19.7, 43.9 (2 steps).
+void channel_pipeline(int prec, int nx, int ny, int64_t S, StepShape *s) {
+    int W, strips, K = 0, M = 0;
+    s->fwin = 3;
+    s->fuse = channel_strips_max_n(prec);
+    row_strips(prec, nx, s->fuse, &W, &strips);
+    double cost = 0.0, cost4 = 0.0;
+    s->fty = chunk_rows(ny, S * strips, 3 * (s->fuse - 1), 1, &cost);
+    if (prec == UQ_FP64 || !rows_shape(prec, 4, RING_ROWS_CH, nx, &K, &M)) return;
+    const int rows = chunk_rows(ny, S, 9, pipeline_per_cu(prec, 4, RING_ROWS_CH, K, M), &cost4);
+    if (cost4 / 4 > cost / s->fuse) return;
+    s->fwin = 2;
+    s->fuse = 4;
+    s->fty = rows;
 }
 
 // The pipeline that carries a job whose shape and layout nobody chose, if one
@@ -65,16 +88,21 @@ static int pipeline_per_cu(int prec, int n, int rows, int K, int M) {
 // step: FP64 64^2 x 5 samples 2.91 -> 2.38, 64^2 x 64 6.28 -> 3.39, FP32 96^2
 // x 3 2.53 -> 1.99, 128^2 x 135 23.5 -> 8.0, 1024^2 x 16 238 -> 44.
 static bool default_pipeline(const uq_problem &p, int64_t S, StepShape *s) {
-    if (p.geometry != UQ_GEOM_TGV || p.layout != UQ_LAYOUT_AUTO) return false;
+    if (p.layout != UQ_LAYOUT_AUTO || needs_ab(p)) return false;
+    const bool channel = p.geometry == UQ_GEOM_CHANNEL;
     const int64_t plane = (int64_t)p.ny * row_pitch(p.nx) + 64;
     const int64_t b = storage_bytes(p.precision), slab = S * 9 * plane * b;
-    if (9 * plane * b >= ((int64_t)1 << 31)) return false;
+    if (9 * plane * b >= ((int64_t)1 << 31) || (channel && plane * 4 >= ((int64_t)1 << 31))) return false;
     // the second slab may take a quarter of the card: a job that only just
     // fits keeps to one
     if (slab > ((int64_t)72 << 30)) return false;
     s->layout = UQ_LAYOUT_AB;
     s->pad = 64;
     s->nt = 0;
+    if (channel) {
+        channel_pipeline(p.precision, p.nx, p.ny, S, s);
+        return true;
+    }
     int K = 0, M = 0;
     s->fuse = p.nx > 128 ? 8 : (p.precision != UQ_FP64 && S * p.ny <= 256 * 12 ? 8 : 6);
     if (rows_shape(p.precision, s->fuse, RING_ROWS_TGV, p.nx, &K, &M)) {
@@ -169,11 +197,11 @@ void Job::release_graph() {
 // steps per fused launch in effect (0: none)
 int Job::fused_n() const {
     if (shape.fuse < 2) return 0;
-    if (jd.geom == 1)  // channel: whole rows, up to 4 steps, where the LDS rows fit
-        return (shape.fwin == 2 && shape.fuse <= 4 && channel_fusable(jd) &&
-                jd.nx <= channel_rows_max_nx(jd.prec, shape.fuse))
-                   ? shape.fuse
-                   : 0;
+    if (jd.geom == 1) {  // channel: whole rows, up to 4 steps, where the LDS rows fit; strips, 3 or more
+        if (!channel_fusable(jd)) return 0;
+        if (shape.fwin == 3) return shape.fuse >= 3 && shape.fuse <= channel_strips_max_n(jd.prec) ? shape.fuse : 0;
+        return shape.fwin == 2 && shape.fuse <= 4 && jd.nx <= channel_rows_max_nx(jd.prec, shape.fuse) ? shape.fuse : 0;
+    }
     const int nmax = shape.fwin >= 2 ? 8 : 4;  // whole rows and their strips: up to 8 steps
     if (shape.fwin == 3 && shape.fuse < 3) return 0;
     return (shape.fuse <= nmax && fused_supported(jd)) ? shape.fuse : 0;

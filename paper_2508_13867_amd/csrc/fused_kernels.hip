@@ -954,6 +954,295 @@ __global__ __launch_bounds__(64 * N * K) void k_stepRC_multi(const FusedJob *job
                                    (int)(local - smp * q.chunks), rq);
     }
 }
+
+// ------------------------------------------------------------------ fused channel steps, strips
+// The row pipeline down strips (STRIP in stepR_item) on the channels that
+// stepRC_item takes, with the bounce-back on the writing side: a node hands
+// f*_opp(i) on as its own f_i where its pull from x - c_i would meet a wall,
+// writing it into the place in the rings where its solid neighbour would have
+// put that pull. The reading side is then the periodic one (unconditional
+// reads at the lane's own column, c_y >= 0 a row ahead), and only waves that
+// hold a wall node pay, per such direction. The places lie in the row the node
+// is in (c_iy = 0), the one before (c_iy = 1, written a step ago and not yet
+// read) or the next (c_iy = -1: one more slot than the periodic rings keep, so
+// that the row being read is left alone). No other lane writes them: solid
+// nodes hand nothing on, and rows beyond the walls are not computed.
+// A strip wraps around the lattice in x as the periodic one does; what comes
+// in through an open end is then overwritten by its rule.
+// 24 direction-rows of 128 columns per level, where the whole rows of
+// stepRC_item keep 30 of up to 512: 6 to 8 steps per launch on any width
+// instead of 2 to 4, and few samples make more work items.
+template <int P, int N>
+struct RowsRingCS {
+    static constexpr int NR = N > 1 ? N - 1 : 1;
+    static constexpr int CW = 64 * RowStrips<P>::M, MR = 2 * N;
+    typename Prec<P>::C f[NR][8][3][CW];
+    // the node masks of the last 2N rows of level 1, for the levels above: a
+    // load of their own each row would wait, on the last level, for the stores
+    // of the row before as well (one counter serves both: 1.9 us per row step,
+    // whatever N)
+    uint32_t mask[MR][CW];
+};
+
+template <int P, int N, int D>
+__device__ __forceinline__ void stepRCS_item(const JobDev &j, const int64_t *d_t, int k0, bool src2, int H,
+                                             int64_t smp, int chunk, RowsRingCS<P, N> &rg, int x0, int W) {
+    using PR = Prec<P>;
+    using C = typename PR::C;
+    using T = typename PR::T;
+    constexpr int M = RowStrips<P>::M, RG = N - 1, CW = RowsRingCS<P, N>::CW, MR = RowsRingCS<P, N>::MR;
+    constexpr uint32_t BB_BITS = 0x1FFu << M_BB, OPEN_BITS = 0x1FFu << M_OPEN;
+    const T *src_all = (const T *)(src2 ? j.f2 : j.f);
+    T *dst_all = (T *)(src2 ? j.f : j.f2);
+    const int nx = j.nx, ny = j.ny;
+    const int plane = (int)j.plane;
+    const int plane_b = plane * (int)sizeof(T), pitch_b = (int)j.pitch * (int)sizeof(T);
+    const float inv = j.inv_scale, sc = j.scale;
+    const int lane = threadIdx.x & 63;
+    const int lvl = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) + 1;  // 1..N
+    const int64_t t_lvl = *d_t + k0 + (lvl - 1);
+    int gx[M], vo0[M], vom[M], vop[M];
+    bool st[M];  // the column is stored
+    // LDS byte offsets of the lane's columns (see stepR_item)
+    constexpr int GB = CW * (int)sizeof(C), SB = 3 * GB, RB = 8 * SB;
+    char *const ring = reinterpret_cast<char *>(&rg.f);
+    int ox[M], om[M], op[M], orx[M];
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const int c = m * 64 + lane;
+        gx[m] = wrap_coord(x0 - RG + c, nx);
+        st[m] = c >= RG && c < RG + W;
+        vo0[m] = gx[m] * (int)sizeof(T);
+        vom[m] = (gx[m] == 0 ? nx - 1 : gx[m] - 1) * (int)sizeof(T);
+        vop[m] = (gx[m] == nx - 1 ? 0 : gx[m] + 1) * (int)sizeof(T);
+        ox[m] = (lvl - 1) * RB + c * (int)sizeof(C);
+        om[m] = (lvl - 1) * RB + (c == 0 ? CW - 1 : c - 1) * (int)sizeof(C);
+        op[m] = (lvl - 1) * RB + (c == CW - 1 ? 0 : c + 1) * (int)sizeof(C);
+        orx[m] = (lvl - 2) * RB + c * (int)sizeof(C);
+    }
+    auto at = [&](int base, int slot, int g) -> C & { return *reinterpret_cast<C *>(ring + base + slot * SB + g * GB); };
+    auto fresh = [&]() {
+#pragma unroll
+        for (int m = 0; m < M; ++m) asm("" : "+v"(ox[m]), "+v"(om[m]), "+v"(op[m]), "+v"(orx[m]));
+    };
+    const __amdgpu_buffer_rsrc_t mrsrc = make_rsrc(j.mask, ny * (int)j.pitch * 4);
+    const int span = RG - (lvl - 1);  // rows beyond the chunk on each side
+    constexpr int B = D + 1;
+    using R = typename BufLd<P>::R;
+    R buf[B][M][9];
+    const int yb = chunk * H, ye = min(ny, yb + H);
+    const int y_lo = max(0, yb - span), y_hi = min(ny, ye + span);  // this level's rows
+    const T *src = src_all + smp * 9 * (int64_t)plane;
+    T *dst = dst_all + smp * 9 * (int64_t)plane;
+    const C omega = (C)j.smp[smp].omega;
+    // s(t) 4 u_peak of this level's step (uniform)
+    const double a_in = ramp_factor(t_lvl, j.ramp) * 4.0 * j.smp[smp].u_peak;
+    const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(src, 9 * plane_b), wrsrc = make_rsrc(dst, 9 * plane_b);
+    auto clampy = [&](int y) { return y < 0 ? 0 : (y >= ny ? ny - 1 : y); };
+    auto pullm = [&](uint32_t *mm, int y) {
+        const int mo = clampy(y) * (int)j.pitch * 4;
+#pragma unroll
+        for (int m = 0; m < M; ++m) mm[m] = __builtin_amdgcn_raw_buffer_load_b32(mrsrc, gx[m] * 4, mo, 0);
+    };
+    // Level 1's pulls of a row whose masks mm are known: the wall rule selects
+    // each lane's address (the node's own opposite population), for every row
+    // (a branch for the waves that hold a wall node leaves copies of the load
+    // buffers, which wait for them).
+    auto pull = [&](R (*f)[9], int y, const uint32_t *mm) {
+        const int gy = clampy(y);
+        const int r0 = gy * pitch_b, rm = (gy == 0 ? ny - 1 : gy - 1) * pitch_b,
+                  rp = (gy == ny - 1 ? 0 : gy + 1) * pitch_b;
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+#pragma unroll
+            for (int i = 0; i < 9; ++i) {
+                const int vo = CXd[i] > 0 ? vom[m] : (CXd[i] < 0 ? vop[m] : vo0[m]);
+                const int ro = CYd[i] > 0 ? rm : (CYd[i] < 0 ? rp : r0);
+                const int from = vo + i * plane_b + ro, own = vo0[m] + OPPd[i] * plane_b + r0;
+                f[m][i] = BufLd<P>::raw(rsrc, ((mm[m] >> (M_BB + i)) & 1u) ? own : from, 0);
+            }
+    };
+    // Slots by the row step a row is written in (see stepR_item): c_y = -1 in
+    // 0-2 and c_y = +1 in 5-7, each step mod 3, c_y = 0 in 3-4, step mod 2;
+    // read one step later, the c_y = +1 ones two.
+    auto put = [&](int u, int m, const C *v) {
+        const int s3 = u % 3, sb = 3 + (u & 1);
+        at(ox[m], s3, 0) = v[4];
+        at(ox[m], sb, 0) = v[0];
+        at(om[m], s3, 1) = v[7];
+        at(om[m], sb, 2) = v[3];
+        at(op[m], s3, 2) = v[8];
+        at(op[m], sb, 1) = v[1];
+        at(ox[m], 5 + s3, 0) = v[2];
+        at(op[m], 5 + s3, 1) = v[5];
+        at(om[m], 5 + s3, 2) = v[6];
+    };
+    auto bounce = [&](int u, int m, uint32_t mm, const C *v) {
+        const int next = (u + 1) % 3, prev = (u + 2) % 3, sb = 3 + (u & 1);
+#pragma unroll
+        for (int i = 1; i < 9; ++i)
+            if ((mm >> (M_BB + i)) & 1u)
+                at(ox[m], CYd[i] < 0 ? next : (CYd[i] == 0 ? sb : 5 + prev), GJd[i]) = v[OPPd[i]];
+    };
+    // the open-column rule, then collide, then hand on or store
+    auto finish = [&](C (*f)[9], const uint32_t *mm, int y, int u) {
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            if (mm[m] & OPEN_BITS) {
+                // (which pulls need zeroing: see stepRC_item)
+                if (t_lvl == 0 || nx == 1) {
+#pragma unroll
+                    for (int i = 0; i < 9; ++i) f[m][i] = ((mm[m] >> (M_OPEN + i)) & 1u) ? C(0) : f[m][i];
+                }
+                if (t_lvl > 0) zou_he_u(f[m], gx[m] == 0, gx[m] == 0 ? (C)inflow_u_a(a_in, ny, y) : C(0));
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            C drho, ux, uy;
+            bgk(f[m], omega, drho, ux, uy);
+        }
+        if (lvl < N) {
+#pragma unroll
+            for (int m = 0; m < M; ++m)
+#pragma unroll
+                for (int i = 0; i < 9; ++i) f[m][i] = PR::rt(f[m][i], sc, inv);
+            uint32_t any = 0;
+#pragma unroll
+            for (int m = 0; m < M; ++m) any |= mm[m];
+            // (uniform: most waves hold neither solid nodes nor their neighbours)
+            if (!__any((any & (BB_BITS | M_SOLID)) != 0)) {
+#pragma unroll
+                for (int m = 0; m < M; ++m) put(u, m, f[m]);
+            } else {
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    if (!(mm[m] & M_SOLID)) put(u, m, f[m]);
+                    if (mm[m] & BB_BITS) bounce(u, m, mm[m], f[m]);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                if (!st[m] || (mm[m] & M_SOLID)) continue;
+#pragma unroll
+                for (int i = 0; i < 9; ++i) BufSt<P>::st(wrsrc, f[m][i], vo0[m], i * plane_b + y * pitch_b, sc);
+            }
+        }
+    };
+    const int y_first = yb - RG - 2 * (lvl - 1);  // this level's row at step 0
+    const int n_it = (ye - yb) + 3 * RG;
+    static_assert(6 % B == 0, "the row loops turn over six steps");
+    if (lvl == 1) {
+        // masks four rows ahead (the pulls, D rows ahead, need them)
+        uint32_t mb[6][M];
+        int ms = 0;  // this step's row of the mask ring
+#pragma unroll
+        for (int k = 0; k < 4; ++k) pullm(mb[k], y_first + k);
+#pragma unroll
+        for (int k = 0; k < D; ++k) pull(buf[k], y_first + k, mb[k]);
+        for (int it0 = 0; it0 < n_it; it0 += 6) {
+#pragma unroll
+            for (int u = 0; u < 6; ++u) {
+                const int it = it0 + u;
+                if (it >= n_it) break;
+                const int y = y_first + it;
+                if (u == 0) fresh();
+                if (y < y_hi) {
+                    pullm(mb[(u + 4) % 6], y + 4);
+                    pull(buf[(u + D) % B], y + D, mb[(u + D) % 6]);
+                    if (y >= y_lo) {
+                        C f[M][9];
+#pragma unroll
+                        for (int m = 0; m < M; ++m) rg.mask[ms][m * 64 + lane] = mb[u][m];
+#pragma unroll
+                        for (int m = 0; m < M; ++m)
+#pragma unroll
+                            for (int i = 0; i < 9; ++i) f[m][i] = BufLd<P>::cvt(buf[u % B][m][i], inv);
+                        finish(f, mb[u], y, u);
+                    }
+                }
+                if (++ms == MR) ms = 0;
+                __syncthreads();
+            }
+        }
+    } else {
+        C pre[2][M][6];
+        int ms = MR - 2 * (lvl - 1);  // the mask ring's row of this level's row: 2 (lvl - 1) steps old
+        for (int it0 = 0; it0 < n_it; it0 += 6) {
+#pragma unroll
+            for (int u = 0; u < 6; ++u) {
+                const int it = it0 + u, k = u & 1;
+                if (it >= n_it) break;
+                const int y = y_first + it;  // this level's row (wave-uniform)
+                if (u == 0) fresh();
+                if (y >= y_lo - 1 && y < y_hi) {
+                    // row y's c_y = -1 pulls and the next row's others
+                    const int s3 = (u + 2) % 3, sb = 3 + ((u + 1) & 1), sc3 = 5 + (u + 1) % 3;
+                    C f[M][9];
+                    C (*q)[6] = pre[k ^ 1];
+                    uint32_t mm[M];
+#pragma unroll
+                    for (int m = 0; m < M; ++m) {
+                        mm[m] = rg.mask[ms][m * 64 + lane];
+                        f[m][4] = at(orx[m], s3, 0);
+                        f[m][7] = at(orx[m], s3, 1);
+                        f[m][8] = at(orx[m], s3, 2);
+                        q[m][0] = at(orx[m], sb, 0);   // (0, 0)
+                        q[m][1] = at(orx[m], sb, 1);   // (1, 0)
+                        q[m][3] = at(orx[m], sb, 2);   // (-1, 0)
+                        q[m][2] = at(orx[m], sc3, 0);  // (0, 1)
+                        q[m][4] = at(orx[m], sc3, 1);  // (1, 1)
+                        q[m][5] = at(orx[m], sc3, 2);  // (-1, 1)
+                        f[m][0] = pre[k][m][0];
+                        f[m][1] = pre[k][m][1];
+                        f[m][2] = pre[k][m][2];
+                        f[m][3] = pre[k][m][3];
+                        f[m][5] = pre[k][m][4];
+                        f[m][6] = pre[k][m][5];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (y >= y_lo) finish(f, mm, y, u);
+                }
+                if (++ms == MR) ms = 0;
+                __syncthreads();
+            }
+        }
+    }
+}
+
+// strip runs fastest, as in k_stepRS
+template <int P, int N, int D>
+__global__ __launch_bounds__(64 * N, 2) void k_stepRCS(
+    JobDev j, const int64_t *d_t, int k0, bool src2, int W, int strips, int H, int chunks, int64_t nwork) {
+    __shared__ RowsRingCS<P, N> rg;
+    const int64_t G = gridDim.x;
+    for (int64_t wk = xcd_logical(blockIdx.x, G); wk < nwork; wk += G) {
+        const int64_t smp = wk / ((int64_t)chunks * strips);
+        const int rem = (int)(wk - smp * chunks * strips);
+        const int chunk = rem / strips;
+        const int x0 = min((rem - chunk * strips) * W, j.nx - W);
+        stepRCS_item<P, N, D>(j, d_t, k0, src2, H, smp, chunk, rg, x0, W);
+    }
+}
+
+// Batched form (see k_stepRC_multi)
+template <int P, int N, int D>
+__global__ __launch_bounds__(64 * N, 2) void k_stepRCS_multi(const FusedJob *jobs, int njobs,
+                                                                                  int64_t nwork, int launch) {
+    __shared__ RowsRingCS<P, N> rg;
+    const int64_t G = gridDim.x;
+    for (int64_t wk = xcd_logical(blockIdx.x, G); wk < nwork; wk += G) {
+        const FusedJob q = fused_entry(jobs, njobs, wk);
+        const JobDev j = q.j;
+        const int64_t local = wk - q.work0;
+        const int64_t smp = local / ((int64_t)q.chunks * q.strips);
+        const int rem = (int)(local - smp * q.chunks * q.strips);
+        const int chunk = rem / q.strips;
+        const int x0 = min((rem - chunk * q.strips) * q.W, j.nx - q.W);
+        stepRCS_item<P, N, D>(j, q.d_t, launch * N, ((q.par ^ launch) & 1) != 0, q.H, smp, chunk, rg, x0, q.W);
+    }
+}
 // ------------------------------------------------------------------ launchers
 template <int P, int N>
 static void stepN_p(const JobDev &j, bool src2, int fty, hipStream_t s) {
@@ -1039,6 +1328,16 @@ static void stepRC_p(const JobDev &j, const int64_t *d_t, int k, bool src2, int 
     UQ_ROWS_CASES(UQ_ROWS_CASE)
 #undef UQ_ROWS_CASE
 }
+template <int P, int N>
+static void stepRCS_p(const JobDev &j, const int64_t *d_t, int k, bool src2, int rows, hipStream_t s) {
+    int W, strips;
+    row_strips(P, j.nx, N, &W, &strips);
+    const int H = std::max(8, std::min(rows, j.ny));
+    const int chunks = (j.ny + H - 1) / H;
+    const int64_t nwork = (int64_t)j.S * strips * chunks;
+    const int64_t G = std::min<int64_t>(nwork, 0x7fffffff);
+    k_stepRCS<P, N, 2><<<(unsigned)G, 64 * N, 0, s>>>(j, d_t, k, src2, W, strips, H, chunks, nwork);
+}
 template <int P, int N, int K, int M>
 static void multi_k(int kind, const FusedJob *jobs, int njobs, int64_t nwork, int launch, hipStream_t s) {
     const int64_t G = std::min<int64_t>(nwork, 0x7fffffff);
@@ -1073,6 +1372,15 @@ bool fused_launch_multi(int kind, int n, int K, int M, const FusedJob *jobs, int
         k_stepRS_multi<P, 8, 2><<<(unsigned)G, 512 * RowStrips<P>::K, 0, s>>>(jobs, njobs, nwork, launch);
         return true;
     }
+    if (kind == 3) {
+        if constexpr (P != UQ_FP64) {
+            if (n != 8) return false;
+            const int64_t G = std::min<int64_t>(nwork, 0x7fffffff);
+            k_stepRCS_multi<P, 8, 2><<<(unsigned)G, 512, 0, s>>>(jobs, njobs, nwork, launch);
+            return true;
+        }
+        return false;
+    }
     if (kind == 0) {
         if (n == 4) return multi_n<P, 4>(0, K, M, jobs, njobs, nwork, launch, s);
         if (n == 6) return multi_n<P, 6>(0, K, M, jobs, njobs, nwork, launch, s);
@@ -1085,8 +1393,16 @@ bool fused_launch_multi(int kind, int n, int K, int M, const FusedJob *jobs, int
     return false;
 }
 template <int P>
-void fused_launch_channel(const JobDev &j, int n, const int64_t *d_t, int k, bool src2, int fty, hipStream_t s) {
-    if (n == 2) stepRC_p<P, 2>(j, d_t, k, src2, fty, s);
+void fused_launch_channel(const JobDev &j, int n, const int64_t *d_t, int k, bool src2, int fty, int window,
+                          hipStream_t s) {
+    if (window == 3) {
+        if (n == 3) stepRCS_p<P, 3>(j, d_t, k, src2, fty, s);
+        else if (n == 4) stepRCS_p<P, 4>(j, d_t, k, src2, fty, s);
+        else if (n == 5) stepRCS_p<P, 5>(j, d_t, k, src2, fty, s);
+        else if (n == 6) stepRCS_p<P, 6>(j, d_t, k, src2, fty, s);
+        else if (n == 7 || P == UQ_FP64) stepRCS_p<P, 7>(j, d_t, k, src2, fty, s);
+        else if constexpr (P != UQ_FP64) stepRCS_p<P, 8>(j, d_t, k, src2, fty, s);
+    } else if (n == 2) stepRC_p<P, 2>(j, d_t, k, src2, fty, s);
     else if (n == 3) stepRC_p<P, 3>(j, d_t, k, src2, fty, s);
     else stepRC_p<P, 4>(j, d_t, k, src2, fty, s);
 }
@@ -1120,7 +1436,7 @@ void fused_launch_tgv(const JobDev &j, int n, bool src2, int fty, int window, bo
 }
 
 template void fused_launch_tgv<UQ_PREC>(const JobDev &, int, bool, int, int, bool, hipStream_t);
-template void fused_launch_channel<UQ_PREC>(const JobDev &, int, const int64_t *, int, bool, int, hipStream_t);
+template void fused_launch_channel<UQ_PREC>(const JobDev &, int, const int64_t *, int, bool, int, int, hipStream_t);
 template bool fused_launch_multi<UQ_PREC>(int, int, int, int, const FusedJob *, int, int64_t, int, hipStream_t);
 
 }  // namespace uqi

@@ -42,8 +42,8 @@ int rows_shape(int prec, int n, int rows, int nx, int *K, int *M);
 #define UQ_ROWS_CASES(CASE) \
     CASE(2, 1) CASE(3, 1) CASE(4, 1) CASE(2, 2) CASE(3, 2) CASE(4, 2) CASE(5, 2) CASE(6, 2)
 
-// The strip form of the row pipeline (window 3, periodic lattices of any
-// width): K waves per level of M columns per lane, WAVES per SIMD at least.
+// The strip form of the row pipelines (window 3, any width): K waves per level
+// of M columns per lane, WAVES per SIMD at least (the channel's: 2).
 template <int P>
 struct RowStrips {
     static constexpr int K = 1, M = 2, WAVES = P == UQ_FP64 ? 2 : 4;
@@ -53,7 +53,8 @@ struct RowStrips {
 template <int P>
 void fused_launch_tgv(const JobDev &j, int n, bool src2, int fty, int window, bool nt, hipStream_t s);
 template <int P>
-void fused_launch_channel(const JobDev &j, int n, const int64_t *d_t, int k, bool src2, int fty, hipStream_t s);
+void fused_launch_channel(const JobDev &j, int n, const int64_t *d_t, int k, bool src2, int fty, int window,
+                          hipStream_t s);
 template <int P>
 bool fused_launch_multi(int kind, int n, int K, int M, const FusedJob *jobs, int njobs, int64_t nwork, int launch,
                         hipStream_t s);

@@ -1025,6 +1025,7 @@ static int rows_max_nx(int prec, int n, int rows) {
 
 int full_rows_max_nx(int prec, int n) { return rows_max_nx(prec, n, RING_ROWS_TGV); }
 int channel_rows_max_nx(int prec, int n) { return rows_max_nx(prec, n, RING_ROWS_CH); }
+int channel_strips_max_n(int prec) { return prec == UQ_FP64 ? 7 : 8; }
 void row_strips(int prec, int nx, int n, int *W, int *strips) {
     const int lanes = prec == UQ_FP64 ? 64 * RowStrips<UQ_FP64>::K * RowStrips<UQ_FP64>::M
                                       : 64 * RowStrips<UQ_FP32>::K * RowStrips<UQ_FP32>::M;
@@ -1041,13 +1042,13 @@ bool channel_fusable(const JobDev &j) {
 // ------------------------------------------------------------------ batched fused launches
 // One launch of a batched fused instance (kind 0: periodic rows,
 // k_stepR_multi; kind 1: channel rows, k_stepRC_multi; kind 2: strips of
-// periodic rows, k_stepRS_multi): every work item of the table's jobs. The
+// periodic rows, k_stepRS_multi; kind 3: of channel rows, k_stepRCS_multi): every work item of the table's jobs. The
 // server keeps to N in {4, 6, 8} (periodic rows), {2, 3, 4} (channel) and 8
 // (strips)
 // and to single precision storage (FP32, FP16S, BF16S), so that a tick of 48
 // steps holds a whole number of launch pairs of every instance.
 int rows_instance(int kind, int prec, int n, int nx, int *K, int *M) {
-    if (kind == 2) {  // strips: any width
+    if (kind >= 2) {  // strips: any width
         *K = *M = 0;
         return 1;
     }
@@ -1055,7 +1056,7 @@ int rows_instance(int kind, int prec, int n, int nx, int *K, int *M) {
 }
 bool fused_multi_supported(int kind, int prec, int n, int K, int M) {
     if (prec == UQ_FP64) return false;
-    if (kind == 2) return n == 8;
+    if (kind >= 2) return n == 8;
     if (kind == 0 ? (n != 4 && n != 6 && n != 8) : (n < 2 || n > 4)) return false;
     return rows_fit(prec, n, kind == 0 ? RING_ROWS_TGV : RING_ROWS_CH, K, M);
 }
@@ -1087,13 +1088,14 @@ hipError_t launch_advance_ptrs(int64_t *const *d_t, int njobs, int64_t n, hipStr
 hipError_t launch_fused(const JobDev &j, int n, bool src2, int fty, int window, bool nt, const int64_t *d_t, int k,
                         hipStream_t s) {
     if (j.geom == 1) {
-        if (!channel_fusable(j) || window != 2 || n < 2 || n > 4 || j.nx > channel_rows_max_nx(j.prec, n))
-            return hipErrorInvalidValue;
+        if (!channel_fusable(j) || (window != 2 && window != 3)) return hipErrorInvalidValue;
+        if (window == 2 && (n < 2 || n > 4 || j.nx > channel_rows_max_nx(j.prec, n))) return hipErrorInvalidValue;
+        if (window == 3 && (n < 3 || n > channel_strips_max_n(j.prec))) return hipErrorInvalidValue;
         switch (j.prec) {
-            case UQ_FP64: fused_launch_channel<UQ_FP64>(j, n, d_t, k, src2, fty, s); break;
-            case UQ_FP32: fused_launch_channel<UQ_FP32>(j, n, d_t, k, src2, fty, s); break;
-            case UQ_FP16S: fused_launch_channel<UQ_FP16S>(j, n, d_t, k, src2, fty, s); break;
-            default: fused_launch_channel<UQ_BF16S>(j, n, d_t, k, src2, fty, s); break;
+            case UQ_FP64: fused_launch_channel<UQ_FP64>(j, n, d_t, k, src2, fty, window, s); break;
+            case UQ_FP32: fused_launch_channel<UQ_FP32>(j, n, d_t, k, src2, fty, window, s); break;
+            case UQ_FP16S: fused_launch_channel<UQ_FP16S>(j, n, d_t, k, src2, fty, window, s); break;
+            default: fused_launch_channel<UQ_BF16S>(j, n, d_t, k, src2, fty, window, s); break;
         }
         return hipGetLastError();
     }

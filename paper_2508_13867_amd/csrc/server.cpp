@@ -130,12 +130,12 @@ static size_t up256(size_t n) { return (n + 255) / 256 * 256; }
 // walls and cylinder, Zou-He or wall or periodic ends) advance N steps per
 // launch over whole rows of H-row chunks in the AB layout; vortex lattices
 // too wide for whole rows at 8 steps, 8 steps per launch in strips of rows
-// (kind 2); kind -1:
+// (kind 2), and channels in strips likewise (kind 3); kind -1:
 // one step per launch in the AA layout (the batched single-step kernel). A shape the
 // launch-shape tuner measured for the job's class is taken when it is a
 // batched instance; otherwise N is the largest of the instance's choices
 // whose LDS rings fit the row width (vortex 8, 6, 4, or 6, 8, 4 up to 128
-// columns; channel 4, 3, 2), the vortex takes equal chunks of at most 256
+// columns; channel 4, else strips at 8), the vortex takes equal chunks of at most 256
 // rows, and the channel cuts its rows into
 // chunks so that its samples fill the GPU (at most 8, as the tuner tries).
 struct ServeShape {
@@ -169,6 +169,7 @@ static ServeShape serve_shape(const uq_problem &p, int64_t S, int K, size_t aren
         if (n < 2 || !rows_instance(kind, p.precision, n, p.nx, &K, &M) ||
             !fused_multi_supported(kind, p.precision, n, K, M))
             continue;
+        if (kind == 1 && c > 0) break;  // fewer steps over whole rows than 4: strips, below
         sh.kind = kind;
         sh.N = n;
         sh.K = K;
@@ -185,6 +186,15 @@ static ServeShape serve_shape(const uq_problem &p, int64_t S, int K, size_t aren
             sh.H = std::max(8, (p.ny + chunks - 1) / chunks);
         }
         return sh;
+    }
+    // channel rows too wide for 4 steps over whole rows: 8 steps per launch in
+    // strips (k_stepRCS), under the same bound on the slabs
+    if (kind == 1 && (p.nx <= 768 || (size_t)job_footprint(p, S, K, true) <= arena * 2 / 5)) {
+        sh.kind = 3;
+        sh.N = 8;
+        row_strips(p.precision, p.nx, sh.N, &sh.W, &sh.strips);
+        const int chunks = (int)std::min<int64_t>(8, std::max<int64_t>(1, (256 + S * sh.strips - 1) / (S * sh.strips)));
+        sh.H = std::max(8, (p.ny + chunks - 1) / chunks);
     }
     // vortex rows too wide for 8 steps over whole rows: 8 steps per launch in
     // strips (k_stepRS; 384^2 x 256 samples: 360k MLUPS against 275k for 4
@@ -345,7 +355,7 @@ void Server::admit() {
         if (r.shape.kind >= 0) {
             sh.layout = UQ_LAYOUT_AB;
             sh.fuse = r.shape.N;
-            sh.fwin = r.shape.kind == 2 ? 3 : 2;
+            sh.fwin = r.shape.kind >= 2 ? 3 : 2;
             sh.fty = r.shape.H;
         } else {
             sh.layout = UQ_LAYOUT_AA;

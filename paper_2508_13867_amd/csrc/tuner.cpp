@@ -13,6 +13,7 @@
 #include <tuple>
 #include <vector>
 
+#include "fused_shapes.h"
 #include "uq_job.h"
 
 namespace uqi {
@@ -144,6 +145,21 @@ extern "C" uq_status uq_autotune(const uq_problem *p, const uq_device *dev, int6
                     s.fwin = 2;
                     cands.push_back(s);
                 }
+            // strips, where a row takes more than one: at most steps per launch
+            // and one less, in the chunks that a job nobody tuned takes
+            if (p->nx > 128)
+                for (int n : {channel_strips_max_n(p->precision), channel_strips_max_n(p->precision) - 1}) {
+                    int W, strips;
+                    row_strips(p->precision, p->nx, n, &W, &strips);
+                    StepShape s;
+                    s.layout = layout;
+                    s.pad = 64;
+                    s.nt = 0;
+                    s.fuse = n;
+                    s.fty = chunk_rows(p->ny, r.S * strips, 3 * (n - 1), 1);
+                    s.fwin = 3;
+                    cands.push_back(s);
+                }
         }
         // 2, 3 or 4 steps per launch (periodic lattices, AB): tiles of 64 x fty
         // nodes, and sliding windows down chunks of fty rows
@@ -171,6 +187,12 @@ extern "C" uq_status uq_autotune(const uq_problem *p, const uq_device *dev, int6
                         s.fuse = n;
                         s.fty = fty;
                         s.fwin = win;
+                        int K, M;
+                        // whole rows: the shorter chunks by the count of rounds
+                        if (win == 2 && fty <= 64 && p->precision != UQ_FP64 &&
+                            rows_shape(p->precision, n, RING_ROWS_TGV, p->nx, &K, &M))
+                            s.fty = chunk_rows(p->ny, r.S, 3 * (n - 1),
+                                               pipeline_per_cu(p->precision, n, RING_ROWS_TGV, K, M));
                         cands.push_back(s);
                     }
         }

@@ -159,7 +159,7 @@ hipError_t launch_step(const JobDev &j, const int64_t *d_t, int k, int parity, c
 // (window 1: the sliding-window kernel with chunks of fty rows, its stores
 // non-temporal if nt; 2: the same over whole rows; 3: the whole-row pipeline
 // down strips; 0: the 64 x fty tile kernel)
-// (channel jobs: window 2 only, advancing the steps t = *d_t + k ..; see
+// (channel jobs: windows 2 and 3, advancing the steps t = *d_t + k ..; see
 // channel_fusable)
 hipError_t launch_fused(const JobDev &j, int n, bool src2, int fty, int window, bool nt, const int64_t *d_t, int k,
                         hipStream_t s);
@@ -168,6 +168,8 @@ hipError_t launch_fused(const JobDev &j, int n, bool src2, int fty, int window, 
 bool channel_fusable(const JobDev &j);
 // widest channel the fused channel kernel takes at this precision and N
 int channel_rows_max_nx(int prec, int n);
+// most steps per launch of the channel's strips
+int channel_strips_max_n(int prec);
 // widest lattice the full-row kernel takes at this precision and N (0: none)
 int full_rows_max_nx(int prec, int n);
 bool fused_supported(const JobDev &j);

@@ -19,7 +19,11 @@ void build_mask(const uq_problem &p, int64_t pitch, std::vector<uint32_t> &mask,
 StepShape choose_shape(const uq_problem &p, int64_t S, bool pipelines = true);
 // Rows per chunk of a pipelined launch: `items` work items per chunk of rows,
 // of which `per_cu` fit a CU, `fill` row steps to fill and drain a pipeline.
-int chunk_rows(int ny, int64_t items, int fill, int per_cu);
+// (cost_out: rounds x row steps of that choice.)
+int chunk_rows(int ny, int64_t items, int fill, int per_cu, double *cost_out = nullptr);
+int pipeline_per_cu(int prec, int n, int rows, int K, int M);
+// window, steps per launch and chunk rows of a channel that nobody tuned
+void channel_pipeline(int prec, int nx, int ny, int64_t S, StepShape *s);
 // tuned shape for a problem class, if one was measured in this process
 bool tuned_shape(const uq_problem &p, int64_t S, StepShape *out);
 
