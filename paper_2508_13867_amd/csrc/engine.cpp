@@ -57,6 +57,30 @@ int pipeline_per_cu(int prec, int n, int rows, int K, int M) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(waves / (n * K), 160 * 1024 / lds));
 }
 
+// Steps per launch of resident tiles for a job, and the time of one step in us,
+// from a fit to one launch of n steps with one tile per CU (single precision
+// 3.45 + 0.54 n us, double 3.6 + 0.81 n) and with more (two share a CU in
+// single precision, at 1.6 times the time). Measured, n = 8: FP32 96^2 x 3
+// samples 7.8 us a launch, FP64 64^2 x 5 10.1.
+double tile_steps(int prec, int nx, int ny, int64_t S, int *n_best) {
+    const bool dbl = prec == UQ_FP64;
+    double best = 0.0;
+    *n_best = 0;
+    // many tiles per CU and a ring to compute in each: never
+    if (S * nx * ny > ((int64_t)1 << 20) && nx * (int64_t)ny > TILE_NODES) return best;
+    for (int n = 3; n <= TILE_MAX_STEPS; ++n) {
+        const TileShape g = tile_shape(nx, ny, n);
+        if (!g.RW) continue;
+        const int64_t rounds = (S * g.tiles_x * g.tiles_y + 255) / 256;
+        const double r = dbl || rounds == 1 ? (double)rounds : 0.8 * (double)rounds;
+        const double t = (dbl ? 0.3 + r * (3.3 + 0.81 * n) : 1.0 + r * (2.45 + 0.54 * n)) / n;
+        if (*n_best && t >= best) continue;
+        best = t;
+        *n_best = n;
+    }
+    return best;
+}
+
 // A channel's pipeline: strips at the most steps per launch, or 4 steps over
 // whole rows where single precision's rings hold them and the count of rounds
 // x row steps per step says so (a row step of either takes about 1.1 us). Us
@@ -80,13 +104,15 @@ void channel_pipeline(int prec, int nx, int ny, int64_t S, StepShape *s) {
 }
 
 // The pipeline that carries a job whose shape and layout nobody chose, if one
-// does (AB layout). Periodic lattices, always: 8 steps per launch over whole rows where
-// the LDS rings hold them, else in strips; up to 128 columns 6 steps (one
-// column per lane; two workgroups per CU in single precision, and the deepest
+// does (AB layout). Channels: channel_pipeline. Periodic lattices, always: 8
+// steps per launch over whole rows where the LDS rings hold them, else in
+// strips; up to 128 columns 6 steps (one column per lane; two workgroups per CU in single precision, and the deepest
 // that double precision's rings hold) unless so few samples ask for it that
-// every chunk gets a CU of its own. Against one step per launch, in us per
-// step: FP64 64^2 x 5 samples 2.91 -> 2.38, 64^2 x 64 6.28 -> 3.39, FP32 96^2
-// x 3 2.53 -> 1.99, 128^2 x 135 23.5 -> 8.0, 1024^2 x 16 238 -> 44.
+// every chunk gets a CU of its own; resident tiles where those are faster
+// still. Us per step, one step per launch and then: the pipelines, FP64 64^2 x
+// 64 samples 6.28 -> 3.39, FP32 128^2 x 135 23.5 -> 8.0, 1024^2 x 16 238 -> 44;
+// resident tiles, FP64 64^2 x 5 2.91 -> 1.20 (the pipeline 2.38), 32^2 x 32 2.78
+// -> 1.04 (2.37), FP32 96^2 x 3 2.53 -> 0.89 (1.99), FP64 64^2 x 64 3.05.
 static bool default_pipeline(const uq_problem &p, int64_t S, StepShape *s) {
     if (p.layout != UQ_LAYOUT_AUTO || needs_ab(p)) return false;
     const bool channel = p.geometry == UQ_GEOM_CHANNEL;
@@ -105,16 +131,32 @@ static bool default_pipeline(const uq_problem &p, int64_t S, StepShape *s) {
     }
     int K = 0, M = 0;
     s->fuse = p.nx > 128 ? 8 : (p.precision != UQ_FP64 && S * p.ny <= 256 * 12 ? 8 : 6);
+    double rows = 0.0;
+    int per_cu;
     if (rows_shape(p.precision, s->fuse, RING_ROWS_TGV, p.nx, &K, &M)) {
         s->fwin = 2;
-        s->fty = chunk_rows(p.ny, S, 3 * (s->fuse - 1), pipeline_per_cu(p.precision, s->fuse, RING_ROWS_TGV, K, M));
+        per_cu = pipeline_per_cu(p.precision, s->fuse, RING_ROWS_TGV, K, M);
+        s->fty = chunk_rows(p.ny, S, 3 * (s->fuse - 1), per_cu, &rows);
     } else {
         int W, strips;
         row_strips(p.precision, p.nx, s->fuse, &W, &strips);
         s->fwin = 3;
-        s->fty = chunk_rows(p.ny, S * strips, 3 * (s->fuse - 1),
-                            pipeline_per_cu(p.precision, s->fuse, RING_ROWS_TGV, RowStrips<UQ_FP32>::K,
-                                            RowStrips<UQ_FP32>::M));
+        M = RowStrips<UQ_FP32>::M;
+        per_cu = pipeline_per_cu(p.precision, s->fuse, RING_ROWS_TGV, RowStrips<UQ_FP32>::K, M);
+        s->fty = chunk_rows(p.ny, S * strips, 3 * (s->fuse - 1), per_cu, &rows);
+    }
+    // Resident tiles instead where they are faster: jobs too small to fill the
+    // card with row chunks. A row step of the pipelines takes, in us, 0.6 (FP64,
+    // one column per lane), 0.9 (two), 0.55 (single precision, 0.8 where two
+    // workgroups share a CU), 0.85 (two columns).
+    const bool dbl = p.precision == UQ_FP64;
+    const double t_row = dbl ? (M == 1 ? 0.6 : 0.9) : (M == 1 ? (rows < 1.0 * (s->fty + 21) ? 0.55 : 0.8) : 0.85);
+    int n = 0;
+    const double t_tile = tile_steps(p.precision, p.nx, p.ny, S, &n);
+    if (n && t_tile < 0.95 * rows * t_row / s->fuse) {
+        s->fwin = 4;
+        s->fuse = n;
+        s->fty = tile_shape(p.nx, p.ny, n).OH;
     }
     return true;
 }
@@ -202,6 +244,10 @@ int Job::fused_n() const {
         if (shape.fwin == 3) return shape.fuse >= 3 && shape.fuse <= channel_strips_max_n(jd.prec) ? shape.fuse : 0;
         return shape.fwin == 2 && shape.fuse <= 4 && jd.nx <= channel_rows_max_nx(jd.prec, shape.fuse) ? shape.fuse : 0;
     }
+    if (shape.fwin == 4)  // resident tiles
+        return shape.fuse <= TILE_MAX_STEPS && fused_supported(jd) && tile_shape(jd.nx, jd.ny, shape.fuse).RW
+                   ? shape.fuse
+                   : 0;
     const int nmax = shape.fwin >= 2 ? 8 : 4;  // whole rows and their strips: up to 8 steps
     if (shape.fwin == 3 && shape.fuse < 3) return 0;
     return (shape.fuse <= nmax && fused_supported(jd)) ? shape.fuse : 0;

@@ -1243,6 +1243,80 @@ __global__ __launch_bounds__(64 * N, 2) void k_stepRCS_multi(const FusedJob *job
         stepRCS_item<P, N, D>(j, q.d_t, launch * N, ((q.par ^ launch) & 1) != 0, q.H, smp, chunk, rg, x0, q.W);
     }
 }
+
+// ------------------------------------------------------------------ fused steps, resident tiles
+// Small periodic jobs, which leave most of the card idle and take the latency
+// of a launch and of its steps: one node per lane, its populations in registers
+// for all n steps of the launch, the eight moving ones exchanged through LDS
+// once per step (two buffers in turn, one barrier). A workgroup takes a region
+// of up to 1024 nodes; in x and in y it is either the whole period, whose ends
+// meet, or an output range with a ring of n - 1 nodes around it, which turns
+// wrong by one node per step and is not stored. The row pipelines take n + (rows
+// of a chunk) + 2 n row steps of 0.5 us for n steps whatever the job's size;
+// here a step takes about as long as one of theirs.
+template <int P>
+__global__ __launch_bounds__(TILE_NODES) void k_stepT(JobDev j, bool src2, int n, TileShape g, int64_t nwork) {
+    using PR = Prec<P>;
+    using C = typename PR::C;
+    using T = typename PR::T;
+    __shared__ C lds[2][8][TILE_NODES];
+    const T *src_all = (const T *)(src2 ? j.f2 : j.f);
+    T *dst_all = (T *)(src2 ? j.f : j.f2);
+    const int nx = j.nx, ny = j.ny, e = threadIdx.x;
+    const int pitch = (int)j.pitch, plane = (int)j.plane;
+    const float inv = j.inv_scale, sc = j.scale;
+    const int rx = g.RW == nx ? 0 : n - 1, ry = g.RH == ny ? 0 : n - 1;  // ring
+    // lanes past the region repeat its last row's nodes and store nothing
+    const int row = e / g.RW, c = e - row * g.RW, r = min(row, g.RH - 1);
+    const bool in = row < g.RH && c >= rx && c < rx + g.OW && r >= ry && r < ry + g.OH;
+    // where each direction is pulled from: across the ends of a whole period,
+    // else (on the region's edge) from the node itself, whatever that gives
+    int from[9];
+#pragma unroll
+    for (int i = 1; i < 9; ++i) {
+        int fr = r - CYd[i], fc = c - CXd[i];
+        fr = fr < 0 ? (ry ? 0 : g.RH - 1) : (fr >= g.RH ? (ry ? g.RH - 1 : 0) : fr);
+        fc = fc < 0 ? (rx ? 0 : g.RW - 1) : (fc >= g.RW ? (rx ? g.RW - 1 : 0) : fc);
+        from[i] = fr * g.RW + fc;
+    }
+    const int64_t G = gridDim.x;
+    for (int64_t wk = xcd_logical(blockIdx.x, G); wk < nwork; wk += G) {
+        const int64_t smp = wk / (g.tiles_x * g.tiles_y);
+        const int rem = (int)(wk - smp * (g.tiles_x * g.tiles_y));
+        const int ty = rem / g.tiles_x, tx = rem - ty * g.tiles_x;
+        // the last tile of a row or column moves back to end at the lattice's
+        const int x0 = min(tx * g.OW, nx - g.OW), y0 = min(ty * g.OH, ny - g.OH);
+        const int gx = wrap_coord(x0 - rx + c, nx), gy = wrap_coord(y0 - ry + r, ny);
+        const T *src = src_all + smp * 9 * (int64_t)plane;
+        T *dst = dst_all + smp * 9 * (int64_t)plane;
+        const C omega = (C)j.smp[smp].omega;
+        const int xm = gx == 0 ? nx - 1 : gx - 1, xp = gx == nx - 1 ? 0 : gx + 1;
+        const int ym = gy == 0 ? ny - 1 : gy - 1, yp = gy == ny - 1 ? 0 : gy + 1;
+        C f[9], drho, ux, uy;
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            const int x = CXd[i] > 0 ? xm : (CXd[i] < 0 ? xp : gx), y = CYd[i] > 0 ? ym : (CYd[i] < 0 ? yp : gy);
+            f[i] = PR::ld(src + (i * plane + y * pitch + x), inv);
+        }
+        bgk(f, omega, drho, ux, uy);
+        for (int s = 1; s < n; ++s) {
+            C(*b)[TILE_NODES] = lds[s & 1];
+            f[0] = PR::rt(f[0], sc, inv);
+#pragma unroll
+            for (int i = 1; i < 9; ++i) b[i - 1][e] = PR::rt(f[i], sc, inv);
+            __syncthreads();
+#pragma unroll
+            for (int i = 1; i < 9; ++i) f[i] = b[i - 1][from[i]];
+            bgk(f, omega, drho, ux, uy);
+        }
+        if (in) {
+            const int own = gy * pitch + gx;
+#pragma unroll
+            for (int i = 0; i < 9; ++i) PR::st(dst + (i * plane + own), f[i], sc);
+        }
+        __syncthreads();  // both buffers are free for the next tile
+    }
+}
 // ------------------------------------------------------------------ launchers
 template <int P, int N>
 static void stepN_p(const JobDev &j, bool src2, int fty, hipStream_t s) {
@@ -1274,6 +1348,15 @@ static void stepW_p(const JobDev &j, bool src2, int rows, bool nt, hipStream_t s
     // rows of loads in flight: 3 (2 at FP64, whose registers are scarcer)
     constexpr int D = P == UQ_FP64 ? 2 : 3;
     k_stepW<P, N, D><<<(unsigned)G, 64 * N, 0, s>>>(j, src2, W, strips, H, chunks, nwork, nt);
+}
+
+template <int P>
+static void stepT_p(const JobDev &j, bool src2, int n, hipStream_t s) {
+    const TileShape g = tile_shape(j.nx, j.ny, n);
+    const int64_t nwork = (int64_t)j.S * g.tiles_x * g.tiles_y;
+    const int64_t G = std::min<int64_t>(nwork, 0x7fffffff);
+    const int threads = (g.RW * g.RH + 63) / 64 * 64;
+    k_stepT<P><<<(unsigned)G, threads, 0, s>>>(j, src2, n, g, nwork);
 }
 
 template <int P, int N>
@@ -1409,7 +1492,9 @@ void fused_launch_channel(const JobDev &j, int n, const int64_t *d_t, int k, boo
 
 template <int P>
 void fused_launch_tgv(const JobDev &j, int n, bool src2, int fty, int window, bool nt, hipStream_t s) {
-    if (window == 3) {
+    if (window == 4) {
+        stepT_p<P>(j, src2, n, s);
+    } else if (window == 3) {
         if (n == 3) stepRS_p<P, 3>(j, src2, fty, s);
         else if (n == 4) stepRS_p<P, 4>(j, src2, fty, s);
         else if (n == 5) stepRS_p<P, 5>(j, src2, fty, s);

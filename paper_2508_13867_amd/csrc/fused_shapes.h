@@ -48,6 +48,15 @@ template <int P>
 struct RowStrips {
     static constexpr int K = 1, M = 2, WAVES = P == UQ_FP64 ? 2 : 4;
 };
+// Regions of the resident-tile kernel (window 4): OW x OH output nodes and the
+// RW x RH <= TILE_NODES nodes computed for them.
+constexpr int TILE_NODES = 1024, TILE_MAX_STEPS = 16;
+struct TileShape {
+    int RW, RH, OW, OH, tiles_x, tiles_y;
+};
+// the fewest tiles for n steps per launch
+TileShape tile_shape(int nx, int ny, int n);
+
 // One fused launch of precision P (see launch_fused, launch_fused_multi):
 // defined in fused_kernels.hip, which is compiled once per precision.
 template <int P>

@@ -1025,6 +1025,26 @@ static int rows_max_nx(int prec, int n, int rows) {
 
 int full_rows_max_nx(int prec, int n) { return rows_max_nx(prec, n, RING_ROWS_TGV); }
 int channel_rows_max_nx(int prec, int n) { return rows_max_nx(prec, n, RING_ROWS_CH); }
+TileShape tile_shape(int nx, int ny, int n) {
+    const int ring = 2 * (n - 1);
+    TileShape best{};
+    for (int tx = 1; tx <= nx; ++tx) {
+        TileShape g;
+        g.OW = (nx + tx - 1) / tx;
+        if (best.RW && g.OW < 8) break;  // (all ring)
+        g.RW = tx == 1 ? nx : g.OW + ring;
+        const int rows = TILE_NODES / std::max(1, g.RW);
+        if (tx > 1 && g.RW >= nx) continue;  // (a ring that meets itself: fewer tiles or narrower ones)
+        g.OH = rows >= ny ? ny : rows - ring;
+        if (g.OH < 1) continue;
+        g.tiles_x = (nx + g.OW - 1) / g.OW;
+        g.tiles_y = (ny + g.OH - 1) / g.OH;
+        g.OH = (ny + g.tiles_y - 1) / g.tiles_y;  // of equal height
+        g.RH = g.tiles_y == 1 && rows >= ny ? ny : g.OH + ring;
+        if (!best.RW || g.tiles_x * g.tiles_y < best.tiles_x * best.tiles_y) best = g;
+    }
+    return best;
+}
 int channel_strips_max_n(int prec) { return prec == UQ_FP64 ? 7 : 8; }
 void row_strips(int prec, int nx, int n, int *W, int *strips) {
     const int lanes = prec == UQ_FP64 ? 64 * RowStrips<UQ_FP64>::K * RowStrips<UQ_FP64>::M
@@ -1099,8 +1119,10 @@ hipError_t launch_fused(const JobDev &j, int n, bool src2, int fty, int window, 
         }
         return hipGetLastError();
     }
-    if (!fused_supported(j) || n < 2 || n > (window >= 2 ? 8 : 4) || (window == 3 && n < 3))
+    if (!fused_supported(j) || n < 2 || n > (window == 4 ? TILE_MAX_STEPS : (window >= 2 ? 8 : 4)) ||
+        (window == 3 && n < 3))
         return hipErrorInvalidValue;
+    if (window == 4 && !tile_shape(j.nx, j.ny, n).RW) return hipErrorInvalidValue;
     if (window == 2 && j.nx > full_rows_max_nx(j.prec, n)) return hipErrorInvalidValue;
     switch (j.prec) {
         case UQ_FP64: fused_launch_tgv<UQ_FP64>(j, n, src2, fty, window, nt, s); break;

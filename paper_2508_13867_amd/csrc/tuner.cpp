@@ -162,19 +162,32 @@ extern "C" uq_status uq_autotune(const uq_problem *p, const uq_device *dev, int6
                 }
         }
         // 2, 3 or 4 steps per launch (periodic lattices, AB): tiles of 64 x fty
-        // nodes, and sliding windows down chunks of fty rows
+        // nodes; resident tiles; and sliding windows down chunks of fty rows
         if (layout == UQ_LAYOUT_AB && p->geometry == UQ_GEOM_TGV) {
             for (int n : {2, 3, 4})
-                for (int pad : {0, 64})
-                    for (int fty : (p->precision == UQ_FP64 ? std::vector<int>{4, 8} : std::vector<int>{8, 16})) {
-                        StepShape s;
-                        s.layout = layout;
-                        s.pad = pad;
-                        s.nt = 1;
-                        s.fuse = n;
-                        s.fty = fty;
-                        cands.push_back(s);
-                    }
+                for (int fty : (p->precision == UQ_FP64 ? std::vector<int>{4, 8} : std::vector<int>{8, 16})) {
+                    StepShape s;
+                    s.layout = layout;
+                    s.pad = 64;
+                    s.nt = 1;
+                    s.fuse = n;
+                    s.fty = fty;
+                    cands.push_back(s);
+                }
+            int n_best;
+            tile_steps(p->precision, p->nx, p->ny, r.S, &n_best);
+            for (int n : {4, 5, 6, 7, 8, std::max(3, n_best)}) {
+                const TileShape g = tile_shape(p->nx, p->ny, n);
+                if (!g.RW) continue;
+                StepShape s;
+                s.layout = layout;
+                s.pad = 64;
+                s.nt = 0;
+                s.fuse = n;
+                s.fty = g.OH;
+                s.fwin = 4;
+                cands.push_back(s);
+            }
             for (int win : {1, 2})
                 for (int n : {2, 3, 4, 5, 6, 7, 8})
                     for (int fty : (p->precision == UQ_FP64 ? std::vector<int>{32, 64} : std::vector<int>{64, 256})) {

@@ -22,6 +22,9 @@ StepShape choose_shape(const uq_problem &p, int64_t S, bool pipelines = true);
 // (cost_out: rounds x row steps of that choice.)
 int chunk_rows(int ny, int64_t items, int fill, int per_cu, double *cost_out = nullptr);
 int pipeline_per_cu(int prec, int n, int rows, int K, int M);
+// steps per launch of resident tiles for a periodic job (0: none), and the time
+// of a step in us
+double tile_steps(int prec, int nx, int ny, int64_t S, int *n);
 // window, steps per launch and chunk rows of a channel that nobody tuned
 void channel_pipeline(int prec, int nx, int ny, int64_t S, StepShape *s);
 // tuned shape for a problem class, if one was measured in this process

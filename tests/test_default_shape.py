@@ -31,7 +31,7 @@ def test_untuned_job_equals_single_steps(prec, nx, ny):
     got = {}
     for layout in (None, "aa"):
         with Job(vortex(nx, ny, prec, **({"layout": layout} if layout else {}))) as job:
-            assert (job.info().fused >= 6) == (layout is None)
+            assert (job.info().fused >= 3) == (layout is None)
             for steps in (1, 16, 26):
                 job.run(steps)
             got[layout] = [job.populations(s) for s in (0, 3)]
