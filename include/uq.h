@@ -287,8 +287,9 @@ typedef struct {
     int32_t plane_pad;  /* padding elements after each population plane */
     int32_t bx;         /* step-kernel workgroup width (height 256/bx) */
     int32_t fused;      /* steps per launch of the fused AB kernel
-                           (tiles and strips 2..4, whole periodic rows
-                           2..8, whole channel rows 2..4), 0 if not
+                           (tiles and window strips 2..4, whole periodic
+                           rows 2..8, whole channel rows 2..4, strips of
+                           either 3..8, resident tiles 3..16), 0 if not
                            fused                                       */
     int32_t fused_rows; /* its tile height (rows of 64 nodes), or the
                            window kernel's chunk height               */
@@ -297,7 +298,8 @@ typedef struct {
                               every population of every sample once)  */
     int32_t fused_window; /* fused kernel: 0 tiles, 1 sliding window
                              down strips, 2 sliding window over whole
-                             rows                                      */
+                             rows, 3 the same down strips, 4 resident
+                             tiles                                     */
     int32_t pad3;
 } uq_job_info;
 
@@ -313,9 +315,9 @@ uq_status uq_samples(const uq_job *job, double *xi, double *a, int64_t *S, int32
 
 /* Advance all samples by `steps` LBM steps (stream + collide with the
  * boundaries inline). Every launch advances all samples: one step per launch,
- * or, in the fused shapes that periodic lattices take by themselves and the
- * tuner picks for them and for simple channels in the AB layout, N = 2..8
- * steps per launch (temporal blocking).
+ * or, in the fused shapes that periodic lattices and channels without
+ * interpolated rules take by themselves or the tuner picks for them (AB
+ * layout), N = 2..16 steps per launch (temporal blocking).
  * Whole blocks of fused launches are replayed from a captured hipGraph; the
  * steps left over run as launches of an odd number (3 or more, at most N) of
  * fused steps, largest first, and the last one or two as single steps, so
@@ -409,7 +411,7 @@ typedef struct {
     int32_t n_candidates;
     int32_t fused;      /* steps per launch of the best if fused (2..8), else 0 */
     int32_t fused_rows; /* its tile height (window: chunk height)              */
-    int32_t fused_window; /* 0 tiles, 1 window strips, 2 window over whole rows */
+    int32_t fused_window; /* as in uq_job_info                                */
 } uq_tune_result;
 uq_status uq_autotune(const uq_problem *p, const uq_device *dev, int64_t steps, uq_tune_result *out);
 
@@ -424,12 +426,11 @@ uq_status uq_autotune(const uq_problem *p, const uq_device *dev, int64_t steps, 
  * lattices and channels with half-way walls, cylinder and Zou-He, wall or
  * periodic ends in single-precision storage run in the AB layout, N steps
  * per launch over whole rows (N from the launch-shape tuner's measurement of
- * the job's class when it has one, else the largest that fits: vortex 8, 6
- * or 4, channel 4, 3 or 2), one launch for all jobs that share a kernel
- * instance; vortex lattices too wide for whole rows run 4 steps per launch
- * in column strips when their two slabs take at most a quarter of the
- * arena; the other jobs (FP64, wide channels, very large vortex jobs) run in
- * the AA layout, one launch per step for all of them. Jobs of different lattices, geometries,
+ * the job's class when it has one, else the largest that fits: vortex 8 or
+ * 6, channel 4), one launch for all jobs that share a kernel instance;
+ * lattices too wide for that run 8 steps per launch in column strips (beyond
+ * 512 columns, channels 768, when their two slabs take at most two fifths of
+ * the arena); the other jobs (FP64, very large ones) run in the AA layout, one launch per step for all of them. Jobs of different lattices, geometries,
  * sample counts and step parities share launches. A job with fewer steps
  * left than a tick takes its last steps in launches of its own. PLAIN mode
  * runs one job at a time and one sample per launch per step (AA), with no
