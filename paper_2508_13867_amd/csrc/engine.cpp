@@ -146,11 +146,11 @@ static bool default_pipeline(const uq_problem &p, int64_t S, StepShape *s) {
         s->fty = chunk_rows(p.ny, S * strips, 3 * (s->fuse - 1), per_cu, &rows);
     }
     // Resident tiles instead where they are faster: jobs too small to fill the
-    // card with row chunks. A row step of the pipelines takes, in us, 0.6 (FP64,
+    // card with row chunks. A row step of the pipelines takes, in us, 0.7 (FP64,
     // one column per lane), 0.9 (two), 0.55 (single precision, 0.8 where two
     // workgroups share a CU), 0.85 (two columns).
     const bool dbl = p.precision == UQ_FP64;
-    const double t_row = dbl ? (M == 1 ? 0.6 : 0.9) : (M == 1 ? (rows < 1.0 * (s->fty + 21) ? 0.55 : 0.8) : 0.85);
+    const double t_row = dbl ? (M == 1 ? 0.7 : 0.9) : (M == 1 ? (rows < 1.0 * (s->fty + 21) ? 0.55 : 0.8) : 0.85);
     int n = 0;
     const double t_tile = tile_steps(p.precision, p.nx, p.ny, S, &n);
     if (n && t_tile < 0.95 * rows * t_row / s->fuse) {
