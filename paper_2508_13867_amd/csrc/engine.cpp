@@ -119,9 +119,16 @@ static bool default_pipeline(const uq_problem &p, int64_t S, StepShape *s) {
     const int64_t plane = (int64_t)p.ny * row_pitch(p.nx) + 64;
     const int64_t b = storage_bytes(p.precision), slab = S * 9 * plane * b;
     if (9 * plane * b >= ((int64_t)1 << 31) || (channel && plane * 4 >= ((int64_t)1 << 31))) return false;
-    // the second slab may take a quarter of the card: a job that only just
-    // fits keeps to one
-    if (slab > ((int64_t)72 << 30)) return false;
+    // A second slab of any size must not be what later jobs miss: it is taken
+    // while a quarter of the card stays free beside both.
+    if (slab > ((int64_t)256 << 20)) {
+        size_t free_b = 0, total_b = 0;
+        if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        if (2 * slab > (int64_t)free_b - (int64_t)(total_b / 4)) return false;
+    }
     s->layout = UQ_LAYOUT_AB;
     s->pad = 64;
     s->nt = 0;
