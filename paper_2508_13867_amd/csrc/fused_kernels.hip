@@ -965,10 +965,14 @@ __global__ __launch_bounds__(64 * N * K) void k_stepRC_multi(const FusedJob *job
 // hold a wall node pay, per such direction. The places lie in the row the node
 // is in (c_iy = 0), the one before (c_iy = 1, written a step ago and not yet
 // read) or the next (c_iy = -1: one more slot than the periodic rings keep, so
-// that the row being read is left alone). No other lane writes them: solid
+// that the row being read is left alone). No other lane may write them: solid
 // nodes hand nothing on, and rows beyond the walls are not computed.
 // A strip wraps around the lattice in x as the periodic one does; what comes
-// in through an open end is then overwritten by its rule.
+// in through an open end is then overwritten by its rule, and where the ends
+// are walls nothing may cross the seam: the columns beside it push towards it
+// into the rows' outermost place (column 0 of c_x = +1, the last of c_x = -1),
+// which no neighbour in the strip fills and whose value never gets to a
+// stored column.
 // 24 direction-rows of 128 columns per level, where the whole rows of
 // stepRC_item keep 30 of up to 512: 6 to 8 steps per launch on any width
 // instead of 2 to 4, and few samples make more work items.
@@ -1001,6 +1005,7 @@ __device__ __forceinline__ void stepRCS_item(const JobDev &j, const int64_t *d_t
     const int lane = threadIdx.x & 63;
     const int lvl = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) + 1;  // 1..N
     const int64_t t_lvl = *d_t + k0 + (lvl - 1);
+    const bool walls = j.xbc == UQ_XBC_WALLS;
     int gx[M], vo0[M], vom[M], vop[M];
     bool st[M];  // the column is stored
     // LDS byte offsets of the lane's columns (see stepR_item)
@@ -1016,8 +1021,8 @@ __device__ __forceinline__ void stepRCS_item(const JobDev &j, const int64_t *d_t
         vom[m] = (gx[m] == 0 ? nx - 1 : gx[m] - 1) * (int)sizeof(T);
         vop[m] = (gx[m] == nx - 1 ? 0 : gx[m] + 1) * (int)sizeof(T);
         ox[m] = (lvl - 1) * RB + c * (int)sizeof(C);
-        om[m] = (lvl - 1) * RB + (c == 0 ? CW - 1 : c - 1) * (int)sizeof(C);
-        op[m] = (lvl - 1) * RB + (c == CW - 1 ? 0 : c + 1) * (int)sizeof(C);
+        om[m] = (lvl - 1) * RB + (c == 0 || (walls && gx[m] == 0) ? CW - 1 : c - 1) * (int)sizeof(C);
+        op[m] = (lvl - 1) * RB + (c == CW - 1 || (walls && gx[m] == nx - 1) ? 0 : c + 1) * (int)sizeof(C);
         orx[m] = (lvl - 2) * RB + c * (int)sizeof(C);
     }
     auto at = [&](int base, int slot, int g) -> C & { return *reinterpret_cast<C *>(ring + base + slot * SB + g * GB); };
