@@ -19,23 +19,26 @@ static int env_int(const char *name, int dflt) {
     return std::atoi(v);
 }
 
+// Rounds that n work items take with `per_cu` of them on a CU at a time. Items
+// that have a CU to themselves run faster: a last round that gives each CU at
+// most one counts 0.6.
+static double rounds_of(int64_t n, int per_cu) {
+    const int64_t slots = (int64_t)256 * per_cu, rest = n % slots;
+    return (double)(n / slots) + (rest == 0 ? 0.0 : (rest <= 256 && per_cu > 1 ? 0.6 : 1.0));
+}
+
 // The chunk count that minimises rounds of work items x row steps per item: a
 // last round that leaves most CUs idle costs as much as a full one, and every
 // chunk pays the pipeline's fill, so neither short nor tall chunks are best
 // by themselves (1024^2 x 16 samples, 9 strips, 8 steps per launch: chunks of
 // 32, 64, 128, 256 rows took 50.2, 44.1, 44.7, 52.4 us per step, in the
-// ratios of this count). Items that have a CU to themselves run faster: a
-// round that gives each CU at most one counts 0.6.
+// ratios of this count).
 int chunk_rows(int ny, int64_t items, int fill, int per_cu, double *cost_out) {
-    const int64_t slots = (int64_t)256 * per_cu;
     double best = 0.0;
     int rows = ny;
     for (int c = 1; c <= std::max(1, ny / 8); ++c) {
         const int H = (ny + c - 1) / c;
-        const int64_t n = items * ((ny + H - 1) / H);
-        const int64_t rest = n % slots;
-        const double rounds = (double)(n / slots) + (rest == 0 ? 0.0 : (rest <= 256 && per_cu > 1 ? 0.6 : 1.0));
-        const double cost = rounds * (H + fill);
+        const double cost = rounds_of(items * ((ny + H - 1) / H), per_cu) * (H + fill);
         if (c == 1 || cost < 0.999 * best) {
             best = cost;
             rows = H;
@@ -88,37 +91,126 @@ double tile_steps(int prec, int nx, int ny, int64_t S, int *n_best) {
 // x 57 x 64 10.5, 8.8; 440 x 82 x 64 13.9, 14.3 (3 steps); x 8 5.0, 6.9; 660 x
 // 123 x 32 20.0, 21.8 (2 steps); 880 x 164 x 32 25.2, one step per launch 53.9;
 // FP64 220 x 41 x 64 8.0, 8.5 (3 steps); 440 x 82 x 64 19.7, 43.9 (2 steps).
-void channel_pipeline(int prec, int nx, int ny, int64_t S, StepShape *s) {
+// Returns us per step, by fits to 1 to 72 rounds of items on lattices of 3 to
+// 2048 rows (9 of 10 of 248 shapes within 18 %): row steps of 1.08 us in strips
+// (16-bit storage 1.17, double 1.25), 1.05 over whole rows (1.15); where all
+// items run at once, 1.1 (1.25, 1.5) and 2 us for the launch, and 0.92 (1.0; with
+// two columns per lane 1.3, 1.4 and the 2 us).
+// A chunk inside the channel also computes its halo; the whole height has none.
+static double channel_pipeline(int prec, int nx, int ny, int64_t S, StepShape *s) {
+    const bool dbl = prec == UQ_FP64, half = storage_bytes(prec) == 2;
     int W, strips, K = 0, M = 0;
     s->fwin = 3;
     s->fuse = channel_strips_max_n(prec);
     row_strips(prec, nx, s->fuse, &W, &strips);
     double cost = 0.0, cost4 = 0.0;
     s->fty = chunk_rows(ny, S * strips, 3 * (s->fuse - 1), 1, &cost);
-    if (prec == UQ_FP64 || !rows_shape(prec, 4, RING_ROWS_CH, nx, &K, &M)) return;
-    const int rows = chunk_rows(ny, S, 9, pipeline_per_cu(prec, 4, RING_ROWS_CH, K, M), &cost4);
-    if (cost4 / 4 > cost / s->fuse) return;
-    s->fwin = 2;
-    s->fuse = 4;
-    s->fty = rows;
+    if (!dbl && rows_shape(prec, 4, RING_ROWS_CH, nx, &K, &M)) {
+        const int per_cu = pipeline_per_cu(prec, 4, RING_ROWS_CH, K, M);
+        const int rows = chunk_rows(ny, S, 9, per_cu, &cost4);
+        if (cost4 / 4 <= cost / s->fuse) {
+            s->fwin = 2;
+            s->fuse = 4;
+            s->fty = rows;
+            const int64_t chunks = (ny + rows - 1) / rows;
+            const double steps = std::min(rows, ny) + (chunks > 1 ? 9 : 6), r = rounds_of(S * chunks, per_cu);
+            if (S * chunks <= 256) return (M == 1 ? steps * (half ? 1.0 : 0.92) : steps * (half ? 1.4 : 1.3) + 2.0) / 4;
+            return r * steps * (half ? 1.15 : 1.05) / 4;
+        }
+    }
+    const int64_t chunks = (ny + s->fty - 1) / s->fty;
+    const double r = rounds_of(S * strips * chunks, 1);
+    const double steps = std::min(s->fty, ny) + (chunks > 1 && r <= 1.0 ? 3 : 2) * (s->fuse - 1);
+    return (r <= 1.0 ? steps * (dbl ? 1.5 : (half ? 1.25 : 1.1)) + 2.0
+                     : r * steps * (dbl ? 1.25 : (half ? 1.17 : 1.08))) / s->fuse;
 }
 
-// The pipeline that carries a job whose shape and layout nobody chose, if one
-// does (AB layout). Channels: channel_pipeline. Periodic lattices, always: 8
-// steps per launch over whole rows where the LDS rings hold them, else in
-// strips; up to 128 columns 6 steps (one column per lane; two workgroups per CU in single precision, and the deepest
+// The pipeline of a periodic lattice: 8 steps per launch over whole rows where
+// the LDS rings hold them, else in strips; up to 128 columns 6 steps (one
+// column per lane; two workgroups per CU in single precision, and the deepest
 // that double precision's rings hold) unless so few samples ask for it that
 // every chunk gets a CU of its own; resident tiles where those are faster
 // still. Us per step, one step per launch and then: the pipelines, FP64 64^2 x
 // 64 samples 6.28 -> 3.39, FP32 128^2 x 135 23.5 -> 8.0, 1024^2 x 16 238 -> 44;
 // resident tiles, FP64 64^2 x 5 2.91 -> 1.20 (the pipeline 2.38), 32^2 x 32 2.78
 // -> 1.04 (2.37), FP32 96^2 x 3 2.53 -> 0.89 (1.99), FP64 64^2 x 64 3.05.
+// Returns us per step: of the tiles' fit, or row steps (whose fill overlaps the
+// item beside it) of 0.77 us with one column per lane (double 0.68, 16-bit
+// storage 0.98) and 0.86 with two (0.98, 1.15): 9 of 10 of 86 shapes of 2 to 4096
+// rows within 20 %.
+static double vortex_pipeline(int prec, int nx, int ny, int64_t S, StepShape *s) {
+    const bool dbl = prec == UQ_FP64, half = storage_bytes(prec) == 2;
+    int K = 0, M = 0, per_cu, strips = 1;
+    s->fuse = nx > 128 ? 8 : (!dbl && S * ny <= 256 * 12 ? 8 : 6);
+    double rows = 0.0;
+    if (rows_shape(prec, s->fuse, RING_ROWS_TGV, nx, &K, &M)) {
+        s->fwin = 2;
+        per_cu = pipeline_per_cu(prec, s->fuse, RING_ROWS_TGV, K, M);
+    } else {
+        int W;
+        row_strips(prec, nx, s->fuse, &W, &strips);
+        s->fwin = 3;
+        M = RowStrips<UQ_FP32>::M;
+        per_cu = pipeline_per_cu(prec, s->fuse, RING_ROWS_TGV, RowStrips<UQ_FP32>::K, M);
+    }
+    s->fty = chunk_rows(ny, S * strips, 3 * (s->fuse - 1), per_cu, &rows);
+    // Resident tiles instead where they are faster: jobs too small to fill the
+    // card with row chunks. A row step of the pipelines takes, in us, 0.7 (FP64,
+    // one column per lane), 0.9 (two), 0.55 (single precision, 0.8 where two
+    // workgroups share a CU), 0.85 (two columns).
+    const double t_row = dbl ? (M == 1 ? 0.7 : 0.9) : (M == 1 ? (rows < 1.0 * (s->fty + 21) ? 0.55 : 0.8) : 0.85);
+    int n = 0;
+    const double t_tile = tile_steps(prec, nx, ny, S, &n);
+    if (n && t_tile < 0.95 * rows * t_row / s->fuse) {
+        s->fwin = 4;
+        s->fuse = n;
+        s->fty = tile_shape(nx, ny, n).OH;
+        return t_tile;
+    }
+    const double r = rounds_of(S * strips * ((ny + s->fty - 1) / s->fty), per_cu);
+    const double steps = std::min(s->fty, ny) + (r <= 1.0 ? 3 : 2) * (s->fuse - 1);
+    return r * steps * (M == 1 ? (dbl ? 0.68 : (half ? 0.98 : 0.77)) : (dbl ? 0.98 : (half ? 1.15 : 0.86))) / s->fuse;
+}
+
+double pipeline_shape(const uq_problem &p, int64_t S, StepShape *s) {
+    s->layout = UQ_LAYOUT_AB;
+    s->pad = 64;
+    s->nt = 0;
+    return p.geometry == UQ_GEOM_CHANNEL ? channel_pipeline(p.precision, p.nx, p.ny, S, s)
+                                         : vortex_pipeline(p.precision, p.nx, p.ny, S, s);
+}
+
+// Us per step of one step per launch in the AA layout: a launch's latency and
+// the longer of the memory traffic (7.5 TB/s where the slab stays in the 256 MB
+// cache, 5.5 beyond) and the lanes' issue, in ps per lane of a row's whole
+// waves (vortices also of whole 4-row tiles): channels 10 (double 13), vortices
+// 4.3 (8.3), from memory 6.5 (10.3). 9 of 10 of 466 shapes, 2 to 1470 us on
+// lattices 2 to 20000 wide x 2 to 600 samples, within 20 %.
+double single_step_us(const uq_problem &p, int64_t S) {
+    const bool channel = p.geometry == UQ_GEOM_CHANNEL, dbl = p.precision == UQ_FP64;
+    const double b = (double)storage_bytes(p.precision), slab = 9.0 * b * (double)S * p.nx * p.ny;
+    const double lanes = (double)S * (channel ? p.ny : (p.ny + 3) / 4 * 4) * (double)row_pitch(p.nx);
+    const bool far = 9.0 * b * lanes > 512e6;
+    const double ps = channel ? (dbl ? 13.0 : 10.0) : (dbl ? (far ? 10.3 : 8.3) : (far ? 6.5 : 4.3));
+    return (channel ? 2.9 : 2.0) + (dbl ? 0.4 : 0.0) +
+           std::max(2.0 * slab / (slab > 256e6 ? 5.5e6 : 7.5e6), lanes * ps * 1e-6);
+}
+
+// The pipeline that carries a job whose shape and layout nobody chose (AB
+// layout), where it is faster than one step per launch. It is not on lattices
+// of few rows, whose pipelines mostly fill and drain, and on channels of few
+// nodes, where a row step's latency counts. Us per step, single steps and
+// pipeline: FP32 vortices 20000 x 2 x 512 samples 270, 288; 4096 x 4 x 512 93,
+// 69; FP16S 32 x 2048 x 32 20.4, 22.8; FP32 channels 400 x 30 x 2 3.4, 4.2 (x 32
+// 8.4, 5.0); 1024 x 8 x 512 46, 58; 4096 x 3 x 512 71, 157 (x 16 rows 437,
+// 282); FP64 500 x 60 x 2 4.2, 5.8 (x 32 23, 15).
 static bool default_pipeline(const uq_problem &p, int64_t S, StepShape *s) {
     if (p.layout != UQ_LAYOUT_AUTO || needs_ab(p)) return false;
     const bool channel = p.geometry == UQ_GEOM_CHANNEL;
     const int64_t plane = (int64_t)p.ny * row_pitch(p.nx) + 64;
     const int64_t b = storage_bytes(p.precision), slab = S * 9 * plane * b;
     if (9 * plane * b >= ((int64_t)1 << 31) || (channel && plane * 4 >= ((int64_t)1 << 31))) return false;
+    if (pipeline_shape(p, S, s) >= single_step_us(p, S)) return false;
     // A second slab of any size must not be what later jobs miss: it is taken
     // while a quarter of the card stays free beside both.
     if (slab > ((int64_t)256 << 20)) {
@@ -128,42 +220,6 @@ static bool default_pipeline(const uq_problem &p, int64_t S, StepShape *s) {
             return false;
         }
         if (2 * slab > (int64_t)free_b - (int64_t)(total_b / 4)) return false;
-    }
-    s->layout = UQ_LAYOUT_AB;
-    s->pad = 64;
-    s->nt = 0;
-    if (channel) {
-        channel_pipeline(p.precision, p.nx, p.ny, S, s);
-        return true;
-    }
-    int K = 0, M = 0;
-    s->fuse = p.nx > 128 ? 8 : (p.precision != UQ_FP64 && S * p.ny <= 256 * 12 ? 8 : 6);
-    double rows = 0.0;
-    int per_cu;
-    if (rows_shape(p.precision, s->fuse, RING_ROWS_TGV, p.nx, &K, &M)) {
-        s->fwin = 2;
-        per_cu = pipeline_per_cu(p.precision, s->fuse, RING_ROWS_TGV, K, M);
-        s->fty = chunk_rows(p.ny, S, 3 * (s->fuse - 1), per_cu, &rows);
-    } else {
-        int W, strips;
-        row_strips(p.precision, p.nx, s->fuse, &W, &strips);
-        s->fwin = 3;
-        M = RowStrips<UQ_FP32>::M;
-        per_cu = pipeline_per_cu(p.precision, s->fuse, RING_ROWS_TGV, RowStrips<UQ_FP32>::K, M);
-        s->fty = chunk_rows(p.ny, S * strips, 3 * (s->fuse - 1), per_cu, &rows);
-    }
-    // Resident tiles instead where they are faster: jobs too small to fill the
-    // card with row chunks. A row step of the pipelines takes, in us, 0.7 (FP64,
-    // one column per lane), 0.9 (two), 0.55 (single precision, 0.8 where two
-    // workgroups share a CU), 0.85 (two columns).
-    const bool dbl = p.precision == UQ_FP64;
-    const double t_row = dbl ? (M == 1 ? 0.7 : 0.9) : (M == 1 ? (rows < 1.0 * (s->fty + 21) ? 0.55 : 0.8) : 0.85);
-    int n = 0;
-    const double t_tile = tile_steps(p.precision, p.nx, p.ny, S, &n);
-    if (n && t_tile < 0.95 * rows * t_row / s->fuse) {
-        s->fwin = 4;
-        s->fuse = n;
-        s->fty = tile_shape(p.nx, p.ny, n).OH;
     }
     return true;
 }

@@ -25,8 +25,11 @@ int pipeline_per_cu(int prec, int n, int rows, int K, int M);
 // steps per launch of resident tiles for a periodic job (0: none), and the time
 // of a step in us
 double tile_steps(int prec, int nx, int ny, int64_t S, int *n);
-// window, steps per launch and chunk rows of a channel that nobody tuned
-void channel_pipeline(int prec, int nx, int ny, int64_t S, StepShape *s);
+// The pipeline of a job that nobody tuned (window, steps per launch, chunk rows;
+// AB layout) and about how many us a step takes in it; the same of one step per
+// launch. (Channels: those with node-local rules.)
+double pipeline_shape(const uq_problem &p, int64_t S, StepShape *s);
+double single_step_us(const uq_problem &p, int64_t S);
 // tuned shape for a problem class, if one was measured in this process
 bool tuned_shape(const uq_problem &p, int64_t S, StepShape *out);
 
