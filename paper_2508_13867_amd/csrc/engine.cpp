@@ -21,10 +21,10 @@ static int env_int(const char *name, int dflt) {
 
 // Rounds that n work items take with `per_cu` of them on a CU at a time. Items
 // that have a CU to themselves run faster: a last round that gives each CU at
-// most one counts 0.6.
-static double rounds_of(int64_t n, int per_cu) {
+// most one counts `alone`.
+double rounds_of(int64_t n, int per_cu, double alone) {
     const int64_t slots = (int64_t)256 * per_cu, rest = n % slots;
-    return (double)(n / slots) + (rest == 0 ? 0.0 : (rest <= 256 && per_cu > 1 ? 0.6 : 1.0));
+    return (double)(n / slots) + (rest == 0 ? 0.0 : (rest <= 256 && per_cu > 1 ? alone : 1.0));
 }
 
 // The chunk count that minimises rounds of work items x row steps per item: a
@@ -38,13 +38,34 @@ int chunk_rows(int ny, int64_t items, int fill, int per_cu, double *cost_out) {
     int rows = ny;
     for (int c = 1; c <= std::max(1, ny / 8); ++c) {
         const int H = (ny + c - 1) / c;
-        const double cost = rounds_of(items * ((ny + H - 1) / H), per_cu) * (H + fill);
+        const double cost = rounds_of(items * ((ny + H - 1) / H), per_cu, 0.6) * (H + fill);
         if (c == 1 || cost < 0.999 * best) {
             best = cost;
             rows = H;
         }
     }
     if (cost_out) *cost_out = best;
+    return std::max(8, rows);
+}
+
+// The chunk height for several jobs in one launch, by the same count: job q has
+// items[q] work items per chunk of its ny[q] rows. Where no CU gets more than one
+// item, a round counts 0.78 here: a lone 1024^2 x 2 takes 7.1 us per step in 432
+// items of 43 rows, 9.6 in 288 of 64 and 8.9 in 216 of 86.
+int group_rows(const int64_t *items, const int *ny, int n, int fill, int per_cu) {
+    const int tallest = *std::max_element(ny, ny + n);
+    double best = 0.0;
+    int rows = tallest;
+    for (int c = 1; c <= std::max(1, tallest / 8); ++c) {
+        const int H = (tallest + c - 1) / c;
+        int64_t work = 0;
+        for (int q = 0; q < n; ++q) work += items[q] * ((ny[q] + H - 1) / H);
+        const double cost = rounds_of(work, per_cu, work <= 256 ? 0.78 : 0.6) * (H + fill);
+        if (c == 1 || cost < 0.999 * best) {
+            best = cost;
+            rows = H;
+        }
+    }
     return std::max(8, rows);
 }
 
@@ -84,6 +105,32 @@ double tile_steps(int prec, int nx, int ny, int64_t S, int *n_best) {
     return best;
 }
 
+// Strips of row pipelines at the most steps per launch: window, steps, chunk rows,
+// and about how many us a step takes, by fits to 1 to 176 rounds of items on
+// lattices of 2 to 1000 rows (9 of 10 of 213 shapes within 20 %). Vortices: row
+// steps, whose fill overlaps the item beside it, of 0.86 us (double 0.98, 16-bit
+// storage 1.15), 0.78 of it for items with a CU to themselves. Channels: 1.08
+// (1.25, 1.17); where all items run at once, 1.1 (1.5, 1.25) and 2 us for the
+// launch. (A chunk inside a channel also computes its halo; the whole height has
+// none.)
+double strips_shape(const uq_problem &p, int64_t S, StepShape *s) {
+    const bool channel = p.geometry == UQ_GEOM_CHANNEL, dbl = p.precision == UQ_FP64;
+    const bool half = storage_bytes(p.precision) == 2;
+    int W, strips;
+    s->fwin = 3;
+    s->fuse = channel ? channel_strips_max_n(p.precision) : 8;
+    row_strips(p.precision, p.nx, s->fuse, &W, &strips);
+    const int per_cu = channel ? 1 : pipeline_per_cu(p.precision, s->fuse, RING_ROWS_TGV, RowStrips<UQ_FP32>::K,
+                                                     RowStrips<UQ_FP32>::M);
+    s->fty = chunk_rows(p.ny, S * strips, 3 * (s->fuse - 1), per_cu);
+    const int64_t chunks = (p.ny + s->fty - 1) / s->fty;
+    const double r = rounds_of(S * strips * chunks, per_cu, 0.78);
+    const double rows = std::min(s->fty, p.ny) + (r <= 1.0 && (!channel || chunks > 1) ? 3 : 2) * (s->fuse - 1);
+    if (!channel) return r * rows * (dbl ? 0.98 : (half ? 1.15 : 0.86)) / s->fuse;
+    return (r <= 1.0 ? rows * (dbl ? 1.5 : (half ? 1.25 : 1.1)) + 2.0
+                     : r * rows * (dbl ? 1.25 : (half ? 1.17 : 1.08))) / s->fuse;
+}
+
 // A channel's pipeline: strips at the most steps per launch, or 4 steps over
 // whole rows where single precision's rings hold them and the count of rounds
 // x row steps per step says so (a row step of either takes about 1.1 us). Us
@@ -91,38 +138,28 @@ double tile_steps(int prec, int nx, int ny, int64_t S, int *n_best) {
 // x 57 x 64 10.5, 8.8; 440 x 82 x 64 13.9, 14.3 (3 steps); x 8 5.0, 6.9; 660 x
 // 123 x 32 20.0, 21.8 (2 steps); 880 x 164 x 32 25.2, one step per launch 53.9;
 // FP64 220 x 41 x 64 8.0, 8.5 (3 steps); 440 x 82 x 64 19.7, 43.9 (2 steps).
-// Returns us per step, by fits to 1 to 72 rounds of items on lattices of 3 to
-// 2048 rows (9 of 10 of 248 shapes within 18 %): row steps of 1.08 us in strips
-// (16-bit storage 1.17, double 1.25), 1.05 over whole rows (1.15); where all
-// items run at once, 1.1 (1.25, 1.5) and 2 us for the launch, and 0.92 (1.0; with
-// two columns per lane 1.3, 1.4 and the 2 us).
-// A chunk inside the channel also computes its halo; the whole height has none.
-static double channel_pipeline(int prec, int nx, int ny, int64_t S, StepShape *s) {
-    const bool dbl = prec == UQ_FP64, half = storage_bytes(prec) == 2;
+// Returns us per step; whole rows by a fit like that of the strips (9 of 10 of 85
+// shapes within 15 %): row steps of 1.05 us (16-bit storage 1.15), where all items
+// run at once 0.92 (1.0; with two columns per lane 1.3, 1.4 and 2 us for the
+// launch).
+static double channel_pipeline(const uq_problem &p, int64_t S, StepShape *s) {
+    const double us = strips_shape(p, S, s);
     int W, strips, K = 0, M = 0;
-    s->fwin = 3;
-    s->fuse = channel_strips_max_n(prec);
-    row_strips(prec, nx, s->fuse, &W, &strips);
+    row_strips(p.precision, p.nx, s->fuse, &W, &strips);
     double cost = 0.0, cost4 = 0.0;
-    s->fty = chunk_rows(ny, S * strips, 3 * (s->fuse - 1), 1, &cost);
-    if (!dbl && rows_shape(prec, 4, RING_ROWS_CH, nx, &K, &M)) {
-        const int per_cu = pipeline_per_cu(prec, 4, RING_ROWS_CH, K, M);
-        const int rows = chunk_rows(ny, S, 9, per_cu, &cost4);
-        if (cost4 / 4 <= cost / s->fuse) {
-            s->fwin = 2;
-            s->fuse = 4;
-            s->fty = rows;
-            const int64_t chunks = (ny + rows - 1) / rows;
-            const double steps = std::min(rows, ny) + (chunks > 1 ? 9 : 6), r = rounds_of(S * chunks, per_cu);
-            if (S * chunks <= 256) return (M == 1 ? steps * (half ? 1.0 : 0.92) : steps * (half ? 1.4 : 1.3) + 2.0) / 4;
-            return r * steps * (half ? 1.15 : 1.05) / 4;
-        }
-    }
-    const int64_t chunks = (ny + s->fty - 1) / s->fty;
-    const double r = rounds_of(S * strips * chunks, 1);
-    const double steps = std::min(s->fty, ny) + (chunks > 1 && r <= 1.0 ? 3 : 2) * (s->fuse - 1);
-    return (r <= 1.0 ? steps * (dbl ? 1.5 : (half ? 1.25 : 1.1)) + 2.0
-                     : r * steps * (dbl ? 1.25 : (half ? 1.17 : 1.08))) / s->fuse;
+    (void)chunk_rows(p.ny, S * strips, 3 * (s->fuse - 1), 1, &cost);
+    if (p.precision == UQ_FP64 || !rows_shape(p.precision, 4, RING_ROWS_CH, p.nx, &K, &M)) return us;
+    const int per_cu = pipeline_per_cu(p.precision, 4, RING_ROWS_CH, K, M);
+    const int rows = chunk_rows(p.ny, S, 9, per_cu, &cost4);
+    if (cost4 / 4 > cost / s->fuse) return us;
+    s->fwin = 2;
+    s->fuse = 4;
+    s->fty = rows;
+    const bool half = storage_bytes(p.precision) == 2;
+    const int64_t chunks = (p.ny + rows - 1) / rows;
+    const double steps = std::min(rows, p.ny) + (chunks > 1 ? 9 : 6);
+    if (S * chunks <= 256) return (M == 1 ? steps * (half ? 1.0 : 0.92) : steps * (half ? 1.4 : 1.3) + 2.0) / 4;
+    return rounds_of(S * chunks, per_cu, 1.0) * steps * (half ? 1.15 : 1.05) / 4;
 }
 
 // The pipeline of a periodic lattice: 8 steps per launch over whole rows where
@@ -134,50 +171,48 @@ static double channel_pipeline(int prec, int nx, int ny, int64_t S, StepShape *s
 // 64 samples 6.28 -> 3.39, FP32 128^2 x 135 23.5 -> 8.0, 1024^2 x 16 238 -> 44;
 // resident tiles, FP64 64^2 x 5 2.91 -> 1.20 (the pipeline 2.38), 32^2 x 32 2.78
 // -> 1.04 (2.37), FP32 96^2 x 3 2.53 -> 0.89 (1.99), FP64 64^2 x 64 3.05.
-// Returns us per step: of the tiles' fit, or row steps (whose fill overlaps the
-// item beside it) of 0.77 us with one column per lane (double 0.68, 16-bit
-// storage 0.98) and 0.86 with two (0.98, 1.15): 9 of 10 of 86 shapes of 2 to 4096
-// rows within 20 %.
-static double vortex_pipeline(int prec, int nx, int ny, int64_t S, StepShape *s) {
-    const bool dbl = prec == UQ_FP64, half = storage_bytes(prec) == 2;
-    int K = 0, M = 0, per_cu, strips = 1;
-    s->fuse = nx > 128 ? 8 : (!dbl && S * ny <= 256 * 12 ? 8 : 6);
-    double rows = 0.0;
-    if (rows_shape(prec, s->fuse, RING_ROWS_TGV, nx, &K, &M)) {
+// Returns us per step: of the tiles' fit, of the strips', or over whole rows as
+// theirs with row steps of 0.77 us at one column per lane (double 0.68, 16-bit
+// storage 0.98; 9 of 10 of 36 shapes within 9 %).
+static double vortex_pipeline(const uq_problem &p, int64_t S, StepShape *s) {
+    const bool dbl = p.precision == UQ_FP64, half = storage_bytes(p.precision) == 2;
+    int K = 0, M = 0;
+    double rows = 0.0, us;
+    s->fuse = p.nx > 128 ? 8 : (!dbl && S * p.ny <= 256 * 12 ? 8 : 6);
+    if (rows_shape(p.precision, s->fuse, RING_ROWS_TGV, p.nx, &K, &M)) {
+        const int per_cu = pipeline_per_cu(p.precision, s->fuse, RING_ROWS_TGV, K, M);
         s->fwin = 2;
-        per_cu = pipeline_per_cu(prec, s->fuse, RING_ROWS_TGV, K, M);
+        s->fty = chunk_rows(p.ny, S, 3 * (s->fuse - 1), per_cu, &rows);
+        const double r = rounds_of(S * ((p.ny + s->fty - 1) / s->fty), per_cu, 0.78);
+        us = r * (std::min(s->fty, p.ny) + (r <= 1.0 ? 3 : 2) * (s->fuse - 1)) *
+             (M == 1 ? (dbl ? 0.68 : (half ? 0.98 : 0.77)) : (half ? 1.15 : 0.86)) / s->fuse;
     } else {
-        int W;
-        row_strips(prec, nx, s->fuse, &W, &strips);
-        s->fwin = 3;
+        int W, strips;
+        us = strips_shape(p, S, s);
+        row_strips(p.precision, p.nx, s->fuse, &W, &strips);
         M = RowStrips<UQ_FP32>::M;
-        per_cu = pipeline_per_cu(prec, s->fuse, RING_ROWS_TGV, RowStrips<UQ_FP32>::K, M);
+        (void)chunk_rows(p.ny, S * strips, 3 * (s->fuse - 1),
+                         pipeline_per_cu(p.precision, s->fuse, RING_ROWS_TGV, RowStrips<UQ_FP32>::K, M), &rows);
     }
-    s->fty = chunk_rows(ny, S * strips, 3 * (s->fuse - 1), per_cu, &rows);
     // Resident tiles instead where they are faster: jobs too small to fill the
     // card with row chunks. A row step of the pipelines takes, in us, 0.7 (FP64,
     // one column per lane), 0.9 (two), 0.55 (single precision, 0.8 where two
     // workgroups share a CU), 0.85 (two columns).
     const double t_row = dbl ? (M == 1 ? 0.7 : 0.9) : (M == 1 ? (rows < 1.0 * (s->fty + 21) ? 0.55 : 0.8) : 0.85);
     int n = 0;
-    const double t_tile = tile_steps(prec, nx, ny, S, &n);
-    if (n && t_tile < 0.95 * rows * t_row / s->fuse) {
-        s->fwin = 4;
-        s->fuse = n;
-        s->fty = tile_shape(nx, ny, n).OH;
-        return t_tile;
-    }
-    const double r = rounds_of(S * strips * ((ny + s->fty - 1) / s->fty), per_cu);
-    const double steps = std::min(s->fty, ny) + (r <= 1.0 ? 3 : 2) * (s->fuse - 1);
-    return r * steps * (M == 1 ? (dbl ? 0.68 : (half ? 0.98 : 0.77)) : (dbl ? 0.98 : (half ? 1.15 : 0.86))) / s->fuse;
+    const double t_tile = tile_steps(p.precision, p.nx, p.ny, S, &n);
+    if (!n || t_tile >= 0.95 * rows * t_row / s->fuse) return us;
+    s->fwin = 4;
+    s->fuse = n;
+    s->fty = tile_shape(p.nx, p.ny, n).OH;
+    return t_tile;
 }
 
 double pipeline_shape(const uq_problem &p, int64_t S, StepShape *s) {
     s->layout = UQ_LAYOUT_AB;
     s->pad = 64;
     s->nt = 0;
-    return p.geometry == UQ_GEOM_CHANNEL ? channel_pipeline(p.precision, p.nx, p.ny, S, s)
-                                         : vortex_pipeline(p.precision, p.nx, p.ny, S, s);
+    return p.geometry == UQ_GEOM_CHANNEL ? channel_pipeline(p, S, s) : vortex_pipeline(p, S, s);
 }
 
 // Us per step of one step per launch in the AA layout: a launch's latency and
@@ -185,14 +220,14 @@ double pipeline_shape(const uq_problem &p, int64_t S, StepShape *s) {
 // cache, 5.5 beyond) and the lanes' issue, in ps per lane of a row's whole
 // waves (vortices also of whole 4-row tiles): channels 10 (double 13), vortices
 // 4.3 (8.3), from memory 6.5 (10.3). 9 of 10 of 466 shapes, 2 to 1470 us on
-// lattices 2 to 20000 wide x 2 to 600 samples, within 20 %.
+// lattices 2 to 20000 wide x 2 to 600 samples, within 25 %.
 double single_step_us(const uq_problem &p, int64_t S) {
     const bool channel = p.geometry == UQ_GEOM_CHANNEL, dbl = p.precision == UQ_FP64;
     const double b = (double)storage_bytes(p.precision), slab = 9.0 * b * (double)S * p.nx * p.ny;
     const double lanes = (double)S * (channel ? p.ny : (p.ny + 3) / 4 * 4) * (double)row_pitch(p.nx);
     const bool far = 9.0 * b * lanes > 512e6;
     const double ps = channel ? (dbl ? 13.0 : 10.0) : (dbl ? (far ? 10.3 : 8.3) : (far ? 6.5 : 4.3));
-    return (channel ? 2.9 : 2.0) + (dbl ? 0.4 : 0.0) +
+    return (channel ? 2.9 : 2.6) + (dbl ? 0.4 : 0.0) +
            std::max(2.0 * slab / (slab > 256e6 ? 5.5e6 : 7.5e6), lanes * ps * 1e-6);
 }
 

@@ -128,16 +128,15 @@ static size_t up256(size_t n) { return (n + 255) / 256 * 256; }
 // The batched instance that carries a job: periodic vortex lattices (kind
 // 0) and channels whose boundary rules are node-local (kind 1: half-way
 // walls and cylinder, Zou-He or wall or periodic ends) advance N steps per
-// launch over whole rows of H-row chunks in the AB layout; vortex lattices
-// too wide for whole rows at 8 steps, 8 steps per launch in strips of rows
-// (kind 2), and channels in strips likewise (kind 3); kind -1:
-// one step per launch in the AA layout (the batched single-step kernel). A shape the
-// launch-shape tuner measured for the job's class is taken when it is a
-// batched instance; otherwise N is the largest of the instance's choices
-// whose LDS rings fit the row width (vortex 8, 6, 4, or 6, 8, 4 up to 128
-// columns; channel 4, else strips at 8), the vortex takes equal chunks of at most 256
-// rows, and the channel cuts its rows into
-// chunks so that its samples fill the GPU (at most 8, as the tuner tries).
+// launch over whole rows of H-row chunks in the AB layout; wider vortex
+// lattices, 8 steps per launch in strips of rows (kind 2), and wider channels
+// likewise (kind 3); kind -1: one step per launch in the AA layout (the batched
+// single-step kernel). A shape the launch-shape tuner measured for the job's
+// class is taken when it is a batched instance; otherwise vortices run 6 steps
+// per launch up to 128 columns, 8 up to 256, and channels 4 where the LDS rings
+// fit the row width; the vortex takes equal chunks of at most 256 rows, and the
+// channel cuts its rows into chunks so that its samples fill the GPU (at most
+// 8, as the tuner tries).
 struct ServeShape {
     int kind = -1, N = 0, K = 0, M = 0, H = 0;
     int W = 0, strips = 1;
@@ -158,18 +157,19 @@ static ServeShape serve_shape(const uq_problem &p, int64_t S, int K, size_t aren
     sh.W = p.nx;
     // vortex lattices of at most 128 columns (one column per lane) run
     // fastest at 6 steps per launch, wider ones at 8 (measured per width on
-    // the serving mix); channels take the deepest pipeline that fits
-    const bool narrow = p.nx <= 128;
-    const int pref[2][3] = {{narrow ? 6 : 8, narrow ? 8 : 0, 0}, {4, 3, 2}};
+    // the serving mix), in 16-bit storage at 4 over whole rows where 8 take
+    // strips: their conversions make row steps dear and bytes cheap (384^2 x
+    // 200 samples 85 against 103 us per step, 512^2 x 100 72 against 83; FP32
+    // 98 and 86, 89 and 70)
+    const int pref[2][2] = {{p.nx <= 128 ? 6 : 8, b == 2 ? 4 : 0}, {4, 0}};
     StepShape tuned;
     const bool have = tuned_shape(p, S, &tuned) && tuned.fwin == 2 && tuned.fuse >= 2;
-    for (int c = -1; c < 3; ++c) {
+    for (int c = -1; c < 2; ++c) {
         const int n = c < 0 ? (have ? tuned.fuse : 0) : pref[kind][c];
         int K = 0, M = 0;
         if (n < 2 || !rows_instance(kind, p.precision, n, p.nx, &K, &M) ||
             !fused_multi_supported(kind, p.precision, n, K, M))
             continue;
-        if (kind == 1 && c > 0) break;  // fewer steps over whole rows than 4: strips, below
         sh.kind = kind;
         sh.N = n;
         sh.K = K;
@@ -187,27 +187,29 @@ static ServeShape serve_shape(const uq_problem &p, int64_t S, int K, size_t aren
         }
         return sh;
     }
-    // channel rows too wide for 4 steps over whole rows: 8 steps per launch in
-    // strips (k_stepRCS), under the same bound on the slabs
-    if (kind == 1 && (p.nx <= 768 || (size_t)job_footprint(p, S, K, true) <= arena * 2 / 5)) {
-        sh.kind = 3;
-        sh.N = 8;
-        row_strips(p.precision, p.nx, sh.N, &sh.W, &sh.strips);
+    // Rows too wide for that: 8 steps per launch in strips (k_stepRCS, k_stepRS;
+    // vortices of 384^2 x 256 samples: 360k MLUPS against 275k for 4 steps over
+    // whole rows, 1024^2 x 64: 414k against 234k for 4 steps in single-wave
+    // strips). Beyond 768 columns (vortices 512) only if the job's two slabs take
+    // at most two fifths of the arena (a larger job would hold back every other
+    // admission; it runs in AA), and not on lattices of few rows, where one step
+    // per launch is faster (a vortex that does not fill the card shares the
+    // launches of others in strips: 4096 x 8 x 2 samples in FP16S 3.0 us per step,
+    // alone in single steps 3.4).
+    StepShape st;
+    const double us = strips_shape(p, S, &st);
+    row_strips(p.precision, p.nx, 8, &sh.W, &sh.strips);
+    if (p.nx > (kind == 1 ? 768 : 512) &&
+        ((us >= single_step_us(p, S) && (kind == 1 || S * sh.strips > 512)) ||
+         (size_t)job_footprint(p, S, K, true) > arena * 2 / 5))
+        return sh;
+    sh.kind = 2 + kind;
+    sh.N = 8;
+    if (kind == 1) {
         const int chunks = (int)std::min<int64_t>(8, std::max<int64_t>(1, (256 + S * sh.strips - 1) / (S * sh.strips)));
         sh.H = std::max(8, (p.ny + chunks - 1) / chunks);
-    }
-    // vortex rows too wide for 8 steps over whole rows: 8 steps per launch in
-    // strips (k_stepRS; 384^2 x 256 samples: 360k MLUPS against 275k for 4
-    // steps over whole rows, 1024^2 x 64: 414k against 234k for 4 steps in
-    // single-wave strips). Beyond 512 columns only if the job's two slabs
-    // take at most two fifths of the arena (a larger job would hold back
-    // every other admission; it runs in AA).
-    if (kind == 0 && (p.nx <= 512 || (size_t)job_footprint(p, S, K, true) <= arena * 2 / 5)) {
-        sh.kind = 2;
-        sh.N = 8;
-        const int chunks = (p.ny + 127) / 128;
-        sh.H = std::max(8, (p.ny + chunks - 1) / chunks);
-        row_strips(p.precision, p.nx, sh.N, &sh.W, &sh.strips);
+    } else {
+        sh.H = st.fty;  // (each table gives its group one height by the same count)
     }
     return sh;
 }
@@ -480,16 +482,30 @@ uq_status Server::rebuild_table() {
     }
     // an instance whose jobs give fewer work items than the GPU has CUs
     // takes shorter row chunks: more items, each a shorter pipeline (the
-    // extra halo rows cost less than idle CUs). The chunking does not change any node's arithmetic.
+    // extra halo rows cost less than idle CUs). The chunking does not change any
+    // node's arithmetic. Vortex strips: the height that the count of rounds x row
+    // steps gives the whole group (640 x 256 x 4 samples alone: 3.6 us per step in
+    // 13 rows, 11.7 in 128).
     constexpr int64_t kTargetItems = 256;
     for (Group &g : groups) {
-        if (g.kind == 2 || g.nwork >= kTargetItems) continue;
+        if (g.kind != 2 && g.nwork >= kTargetItems) continue;
+        int rows = 0;
+        if (g.kind == 2) {
+            std::vector<int64_t> items;
+            std::vector<int> ny;
+            for (int q = g.first; q < g.first + g.count; ++q) {
+                items.push_back((int64_t)fused[(size_t)q].j.S * fused[(size_t)q].strips);
+                ny.push_back(fused[(size_t)q].j.ny);
+            }
+            rows = group_rows(items.data(), ny.data(), g.count, 3 * (g.N - 1), 2);
+        }
         const int hmin = g.N >= 6 ? 32 : 16;
         int64_t w = 0;
         for (int q = g.first; q < g.first + g.count; ++q) {
             FusedJob &f = fused[(size_t)q];
             const int64_t want = (f.chunks * kTargetItems + g.nwork - 1) / g.nwork;
-            const int H = std::min(f.H, std::max(hmin, (int)((f.j.ny + want - 1) / want)));
+            const int H = rows ? std::min(rows, f.j.ny)
+                               : std::min(f.H, std::max(hmin, (int)((f.j.ny + want - 1) / want)));
             f.chunks = (f.j.ny + H - 1) / H;
             f.H = std::max(8, (f.j.ny + f.chunks - 1) / f.chunks);  // equal chunks
             f.work0 = w;

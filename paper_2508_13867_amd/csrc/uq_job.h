@@ -20,14 +20,18 @@ StepShape choose_shape(const uq_problem &p, int64_t S, bool pipelines = true);
 // Rows per chunk of a pipelined launch: `items` work items per chunk of rows,
 // of which `per_cu` fit a CU, `fill` row steps to fill and drain a pipeline.
 // (cost_out: rounds x row steps of that choice.)
+double rounds_of(int64_t n, int per_cu, double alone);
 int chunk_rows(int ny, int64_t items, int fill, int per_cu, double *cost_out = nullptr);
+int group_rows(const int64_t *items, const int *ny, int n, int fill, int per_cu);
 int pipeline_per_cu(int prec, int n, int rows, int K, int M);
 // steps per launch of resident tiles for a periodic job (0: none), and the time
 // of a step in us
 double tile_steps(int prec, int nx, int ny, int64_t S, int *n);
 // The pipeline of a job that nobody tuned (window, steps per launch, chunk rows;
 // AB layout) and about how many us a step takes in it; the same of one step per
-// launch. (Channels: those with node-local rules.)
+// launch. (Channels: those with node-local rules. strips_shape: the strips at the
+// most steps per launch, whether or not another pipeline is faster.)
+double strips_shape(const uq_problem &p, int64_t S, StepShape *s);
 double pipeline_shape(const uq_problem &p, int64_t S, StepShape *s);
 double single_step_us(const uq_problem &p, int64_t S);
 // tuned shape for a problem class, if one was measured in this process
