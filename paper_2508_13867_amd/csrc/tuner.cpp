@@ -5,8 +5,10 @@
 // cache file (UQ_TUNE_CACHE) carries results across processes.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <map>
 #include <mutex>
 #include <string>
@@ -92,6 +94,153 @@ bool tuned_shape(const uq_problem &p, int64_t S, StepShape *out) {
     return true;
 }
 
+// The shapes that uq_autotune times for a problem of S samples; writes the
+// first `cap` of them to out and returns how many there are.
+int64_t tune_candidates(const uq_problem &p, int64_t S, StepShape *out, int64_t cap) {
+    std::vector<StepShape> cands;
+    auto add = [&](const StepShape &s) {
+        for (const StepShape &c : cands)
+            if (std::memcmp(&c, &s, sizeof s) == 0) return;
+        cands.push_back(s);
+    };
+    for (int layout : {UQ_LAYOUT_AA, UQ_LAYOUT_AB}) {
+        if (p.layout != UQ_LAYOUT_AUTO && p.layout != layout) continue;
+        if (needs_ab(p) && layout != UQ_LAYOUT_AB) continue;
+        for (int bx : {64, 128, 256})
+            for (int cpt : {1, 2})
+                for (int pad : {0, 64})
+                    for (int nt : {0, 1}) {
+                        if (layout == UQ_LAYOUT_AA && nt) continue;  // AA stores are in place
+                        if (bx > 64 && bx / 2 >= p.nx) continue;      // mostly idle lanes
+                        StepShape s;
+                        s.layout = layout;
+                        s.cpt = cpt;
+                        s.pad = pad;
+                        s.nt = nt;
+                        s.bx = bx;
+                        add(s);
+                    }
+        // channels with half-way and Zou-He / wall / periodic ends (AB): the
+        // full-row window, 2 to 4 steps per launch, the height cut into 1 to 8
+        // balanced chunks (a workgroup per chunk and sample: few samples
+        // need several chunks to fill the chip)
+        if (layout == UQ_LAYOUT_AB && p.geometry == UQ_GEOM_CHANNEL && p.cyl_bc == UQ_CYL_HALFWAY &&
+            p.xbc != UQ_XBC_INTERP) {
+            std::vector<int> heights;
+            for (int nch : {1, 2, 3, 4, 6, 8}) {
+                const int h = (p.ny + nch - 1) / nch;
+                if (h >= 8 && (heights.empty() || heights.back() != h)) heights.push_back(h);
+            }
+            for (int n : {2, 3, 4})
+                for (int fty : heights) {
+                    if (p.nx > channel_rows_max_nx(p.precision, n)) continue;
+                    StepShape s;
+                    s.layout = layout;
+                    s.pad = 64;
+                    s.nt = 0;
+                    s.fuse = n;
+                    s.fty = fty;
+                    s.fwin = 2;
+                    add(s);
+                }
+            // strips, where a row takes more than one: at most steps per launch
+            // and one less, in the chunks that a job nobody tuned takes
+            if (p.nx > 128)
+                for (int n : {channel_strips_max_n(p.precision), channel_strips_max_n(p.precision) - 1}) {
+                    int W, strips;
+                    row_strips(p.precision, p.nx, n, &W, &strips);
+                    StepShape s;
+                    s.layout = layout;
+                    s.pad = 64;
+                    s.nt = 0;
+                    s.fuse = n;
+                    s.fty = chunk_rows(p.ny, S * strips, 3 * (n - 1), 1);
+                    s.fwin = 3;
+                    add(s);
+                }
+        }
+        // 2, 3 or 4 steps per launch (periodic lattices, AB): tiles of 64 x fty
+        // nodes; resident tiles; and sliding windows down chunks of fty rows
+        if (layout == UQ_LAYOUT_AB && p.geometry == UQ_GEOM_TGV) {
+            for (int n : {2, 3, 4})
+                for (int fty : (p.precision == UQ_FP64 ? std::vector<int>{4, 8} : std::vector<int>{8, 16})) {
+                    StepShape s;
+                    s.layout = layout;
+                    s.pad = 64;
+                    s.nt = 1;
+                    s.fuse = n;
+                    s.fty = fty;
+                    add(s);
+                }
+            int n_best;
+            tile_steps(p.precision, p.nx, p.ny, S, &n_best);
+            for (int n : {4, 5, 6, 7, 8, std::max(3, n_best)}) {
+                const TileShape g = tile_shape(p.nx, p.ny, n);
+                if (!g.RW) continue;
+                StepShape s;
+                s.layout = layout;
+                s.pad = 64;
+                s.nt = 0;
+                s.fuse = n;
+                s.fty = g.OH;
+                s.fwin = 4;
+                add(s);
+            }
+            for (int win : {1, 2})
+                for (int n : {2, 3, 4, 5, 6, 7, 8})
+                    for (int fty : (p.precision == UQ_FP64 ? std::vector<int>{32, 64} : std::vector<int>{64, 256})) {
+                        if (win == 1 && n > 4) continue;  // strips: up to 4 steps
+                        if (win == 2 && (n < 3 || p.nx > full_rows_max_nx(p.precision, n))) continue;
+                        StepShape s;
+                        s.layout = layout;
+                        s.pad = 64;
+                        s.nt = 0;
+                        s.fuse = n;
+                        s.fty = fty;
+                        s.fwin = win;
+                        int K, M;
+                        // whole rows: the shorter chunks (double precision: these
+                        // too) by the count of rounds
+                        const bool count = win == 2 && fty <= 64 && rows_shape(p.precision, n, RING_ROWS_TGV, p.nx, &K, &M);
+                        if (!count || p.precision == UQ_FP64) add(s);
+                        if (!count) continue;
+                        s.fty = chunk_rows(p.ny, S, 3 * (n - 1),
+                                           pipeline_per_cu(p.precision, n, RING_ROWS_TGV, K, M));
+                        add(s);
+                    }
+        }
+        // rows wider than 8 steps over whole rows take: the same pipeline down
+        // strips, 6 or 8 steps per launch
+        int K8, M8;
+        if (layout == UQ_LAYOUT_AB && p.geometry == UQ_GEOM_TGV &&
+            !rows_shape(p.precision, 8, RING_ROWS_TGV, p.nx, &K8, &M8) && p.nx > 128)
+            for (int n : {6, 8}) {
+                int W, strips;
+                row_strips(p.precision, p.nx, n, &W, &strips);
+                const int per_cu = pipeline_per_cu(p.precision, n, RING_ROWS_TGV, RowStrips<UQ_FP32>::K,
+                                                   RowStrips<UQ_FP32>::M);
+                for (int fty : {64, 256, chunk_rows(p.ny, S * strips, 3 * (n - 1), per_cu)}) {
+                    StepShape s;
+                    s.layout = layout;
+                    s.pad = 64;
+                    s.nt = 0;
+                    s.fuse = n;
+                    s.fty = fty;
+                    s.fwin = 3;
+                    add(s);
+                }
+            }
+        // what the job would run in untuned: a tuned job is never the slower
+        if (layout == UQ_LAYOUT_AB && !needs_ab(p)) {
+            StepShape s;
+            pipeline_shape(p, S, &s);
+            add(s);
+        }
+    }
+    for (int64_t k = 0; k < std::min<int64_t>(cap, (int64_t)cands.size()); ++k) out[k] = cands[(size_t)k];
+    return (int64_t)cands.size();
+}
+
 }  // namespace uqi
 
 using namespace uqi;
@@ -104,130 +253,8 @@ extern "C" uq_status uq_autotune(const uq_problem *p, const uq_device *dev, int6
     uq_status st = build_rule(*p, r);
     if (st != UQ_OK) return st;
 
-    std::vector<StepShape> cands;
-    for (int layout : {UQ_LAYOUT_AA, UQ_LAYOUT_AB}) {
-        if (p->layout != UQ_LAYOUT_AUTO && p->layout != layout) continue;
-        if (needs_ab(*p) && layout != UQ_LAYOUT_AB) continue;
-        for (int bx : {64, 128, 256})
-            for (int cpt : {1, 2})
-                for (int pad : {0, 64})
-                    for (int nt : {0, 1}) {
-                        if (layout == UQ_LAYOUT_AA && nt) continue;  // AA stores are in place
-                        if (bx > 64 && bx / 2 >= p->nx) continue;      // mostly idle lanes
-                        StepShape s;
-                        s.layout = layout;
-                        s.cpt = cpt;
-                        s.pad = pad;
-                        s.nt = nt;
-                        s.bx = bx;
-                        cands.push_back(s);
-                    }
-        // channels with half-way and Zou-He / wall / periodic ends (AB): the
-        // full-row window, 2 to 4 steps per launch, the height cut into 1 to 8
-        // balanced chunks (a workgroup per chunk and sample: few samples
-        // need several chunks to fill the chip)
-        if (layout == UQ_LAYOUT_AB && p->geometry == UQ_GEOM_CHANNEL && p->cyl_bc == UQ_CYL_HALFWAY &&
-            p->xbc != UQ_XBC_INTERP) {
-            std::vector<int> heights;
-            for (int nch : {1, 2, 3, 4, 6, 8}) {
-                const int h = (p->ny + nch - 1) / nch;
-                if (h >= 8 && (heights.empty() || heights.back() != h)) heights.push_back(h);
-            }
-            for (int n : {2, 3, 4})
-                for (int fty : heights) {
-                    if (p->nx > channel_rows_max_nx(p->precision, n)) continue;
-                    StepShape s;
-                    s.layout = layout;
-                    s.pad = 64;
-                    s.nt = 0;
-                    s.fuse = n;
-                    s.fty = fty;
-                    s.fwin = 2;
-                    cands.push_back(s);
-                }
-            // strips, where a row takes more than one: at most steps per launch
-            // and one less, in the chunks that a job nobody tuned takes
-            if (p->nx > 128)
-                for (int n : {channel_strips_max_n(p->precision), channel_strips_max_n(p->precision) - 1}) {
-                    int W, strips;
-                    row_strips(p->precision, p->nx, n, &W, &strips);
-                    StepShape s;
-                    s.layout = layout;
-                    s.pad = 64;
-                    s.nt = 0;
-                    s.fuse = n;
-                    s.fty = chunk_rows(p->ny, r.S * strips, 3 * (n - 1), 1);
-                    s.fwin = 3;
-                    cands.push_back(s);
-                }
-        }
-        // 2, 3 or 4 steps per launch (periodic lattices, AB): tiles of 64 x fty
-        // nodes; resident tiles; and sliding windows down chunks of fty rows
-        if (layout == UQ_LAYOUT_AB && p->geometry == UQ_GEOM_TGV) {
-            for (int n : {2, 3, 4})
-                for (int fty : (p->precision == UQ_FP64 ? std::vector<int>{4, 8} : std::vector<int>{8, 16})) {
-                    StepShape s;
-                    s.layout = layout;
-                    s.pad = 64;
-                    s.nt = 1;
-                    s.fuse = n;
-                    s.fty = fty;
-                    cands.push_back(s);
-                }
-            int n_best;
-            tile_steps(p->precision, p->nx, p->ny, r.S, &n_best);
-            for (int n : {4, 5, 6, 7, 8, std::max(3, n_best)}) {
-                const TileShape g = tile_shape(p->nx, p->ny, n);
-                if (!g.RW) continue;
-                StepShape s;
-                s.layout = layout;
-                s.pad = 64;
-                s.nt = 0;
-                s.fuse = n;
-                s.fty = g.OH;
-                s.fwin = 4;
-                cands.push_back(s);
-            }
-            for (int win : {1, 2})
-                for (int n : {2, 3, 4, 5, 6, 7, 8})
-                    for (int fty : (p->precision == UQ_FP64 ? std::vector<int>{32, 64} : std::vector<int>{64, 256})) {
-                        if (win == 1 && n > 4) continue;  // strips: up to 4 steps
-                        if (win == 2 && (n < 3 || p->nx > full_rows_max_nx(p->precision, n))) continue;
-                        StepShape s;
-                        s.layout = layout;
-                        s.pad = 64;
-                        s.nt = 0;
-                        s.fuse = n;
-                        s.fty = fty;
-                        s.fwin = win;
-                        int K, M;
-                        // whole rows: the shorter chunks by the count of rounds
-                        if (win == 2 && fty <= 64 && p->precision != UQ_FP64 &&
-                            rows_shape(p->precision, n, RING_ROWS_TGV, p->nx, &K, &M))
-                            s.fty = chunk_rows(p->ny, r.S, 3 * (n - 1),
-                                               pipeline_per_cu(p->precision, n, RING_ROWS_TGV, K, M));
-                        cands.push_back(s);
-                    }
-        }
-        // rows wider than 8 steps over whole rows take: the same pipeline down
-        // strips, 6 or 8 steps per launch
-        if (layout == UQ_LAYOUT_AB && p->geometry == UQ_GEOM_TGV && p->nx > 256)
-            for (int n : {6, 8}) {
-                int W, strips;
-                row_strips(p->precision, p->nx, n, &W, &strips);
-                std::vector<int> heights = {64, 256, chunk_rows(p->ny, r.S * strips, 3 * (n - 1), 2)};
-                for (int fty : heights) {
-                    StepShape s;
-                    s.layout = layout;
-                    s.pad = 64;
-                    s.nt = 0;
-                    s.fuse = n;
-                    s.fty = fty;
-                    s.fwin = 3;
-                    cands.push_back(s);
-                }
-            }
-    }
+    std::vector<StepShape> cands((size_t)tune_candidates(*p, r.S, nullptr, 0));
+    tune_candidates(*p, r.S, cands.data(), (int64_t)cands.size());
 
     const double bytes_per_node = 18.0 * (double)storage_bytes(p->precision);
     Entry best;

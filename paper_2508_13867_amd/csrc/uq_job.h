@@ -34,6 +34,8 @@ double tile_steps(int prec, int nx, int ny, int64_t S, int *n);
 double strips_shape(const uq_problem &p, int64_t S, StepShape *s);
 double pipeline_shape(const uq_problem &p, int64_t S, StepShape *s);
 double single_step_us(const uq_problem &p, int64_t S);
+// the shapes uq_autotune times (at most cap of them to out); returns their number
+int64_t tune_candidates(const uq_problem &p, int64_t S, StepShape *out, int64_t cap);
 // tuned shape for a problem class, if one was measured in this process
 bool tuned_shape(const uq_problem &p, int64_t S, StepShape *out);
 
