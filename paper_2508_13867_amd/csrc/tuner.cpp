@@ -112,6 +112,7 @@ int64_t tune_candidates(const uq_problem &p, int64_t S, StepShape *out, int64_t 
                     for (int nt : {0, 1}) {
                         if (layout == UQ_LAYOUT_AA && nt) continue;  // AA stores are in place
                         if (bx > 64 && bx / 2 >= p.nx) continue;      // mostly idle lanes
+                        if (cpt > 1 && needs_ab(p)) continue;         // k_step_interp takes one row
                         StepShape s;
                         s.layout = layout;
                         s.cpt = cpt;
@@ -172,9 +173,12 @@ int64_t tune_candidates(const uq_problem &p, int64_t S, StepShape *out, int64_t 
                     s.fty = fty;
                     add(s);
                 }
+            // (none where the count of tiles rules them out; the fit's own choice
+            // of steps, or twelve where that is among the others)
             int n_best;
             tile_steps(p.precision, p.nx, p.ny, S, &n_best);
-            for (int n : {4, 5, 6, 7, 8, std::max(3, n_best)}) {
+            const int other = n_best >= 4 && n_best <= 8 ? 12 : n_best;
+            for (int n : n_best ? std::vector<int>{4, 5, 6, 7, 8, other} : std::vector<int>()) {
                 const TileShape g = tile_shape(p.nx, p.ny, n);
                 if (!g.RW) continue;
                 StepShape s;
@@ -233,8 +237,7 @@ int64_t tune_candidates(const uq_problem &p, int64_t S, StepShape *out, int64_t 
         // what the job would run in untuned: a tuned job is never the slower
         if (layout == UQ_LAYOUT_AB && !needs_ab(p)) {
             StepShape s;
-            pipeline_shape(p, S, &s);
-            add(s);
+            if (pipeline_shape(p, S, &s) < single_step_us(p, S)) add(s);
         }
     }
     for (int64_t k = 0; k < std::min<int64_t>(cap, (int64_t)cands.size()); ++k) out[k] = cands[(size_t)k];

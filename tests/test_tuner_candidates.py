@@ -39,10 +39,13 @@ def test_the_untuned_shape_is_timed(prec, geometry, nx, ny, S):
     fn.restype = C.c_double
     # what a StepShape holds where the pipeline leaves it alone
     s.cpt, s.bx = 1, 64
-    fn(C.byref(p), C.c_int64(S), C.byref(s))
+    us = fn(C.byref(p), C.c_int64(S), C.byref(s))
+    single = A.lib()["_ZN3uqi14single_step_usERK10uq_probleml"]
+    single.restype = C.c_double
     keys = [c.key() for c in candidates(p, S)]
-    assert s.key() in keys
-    # and one step per launch in either layout
+    # the pipeline, or one step per launch where the job takes that; the
+    # single steps are there in either layout
+    assert s.key() in keys or us >= single(C.byref(p), C.c_int64(S))
     assert {c[3] for c in keys if c[6] < 2} == {1, 2}
 
 
@@ -51,3 +54,20 @@ def test_double_precision_strips_are_timed(nx):
     # its rings hold no more than 4 steps over whole rows there
     got = {(c.fwin, c.fuse) for c in candidates(problem("tgv", "fp64", nx, nx), 64)}
     assert {(3, 6), (3, 8), (2, 4)} <= got and not any(w == 2 and n > 4 for w, n in got)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16s"])
+@pytest.mark.parametrize("nx, ny, S", [(64, 64, 5), (96, 96, 3), (128, 128, 8), (128, 128, 4096), (64, 64, 4096),
+                                       (32, 32, 5000), (1024, 1024, 16)])
+def test_nothing_is_timed_in_vain(prec, nx, ny, S):
+    got = [c.key() for c in candidates(problem("tgv", prec, nx, ny), S)]
+    assert len(set(got)) == len(got)
+    # more tiles than the card takes, with a ring to compute around each
+    if S * nx * ny > 1 << 20 and nx * ny > 1024:
+        assert not any(c[8] == 4 for c in got)
+
+
+def test_interpolated_channels_take_one_row():
+    p = problem("channel", "fp32", 440, 80, cyl_bc="bouzidi", cyl_x=40.0, cyl_y=39.5, cyl_d=20.0, xbc="interp",
+                layout="ab")
+    assert {c.cpt for c in candidates(p, 11)} == {1}
