@@ -376,7 +376,6 @@ __device__ inline void wave_join(NSum &a) {
 // part[sample][chunk] = {KE, Fx, Fy as sum and compensation, count} and are
 // joined by k_qoi_join (one workgroup per sample read 1024^2 nodes x 16
 // samples in 3.2 ms, 0.2 TB/s; latency bound).
-constexpr int QOI_PART = 7;
 template <int P, bool CHANNEL, int MODE>
 __global__ __launch_bounds__(256) void k_qoi(JobDev j, int64_t t, int per, double *part, double *out) {
     using PR = Prec<P>;
@@ -1149,16 +1148,16 @@ hipError_t launch_select_scalar(const JobDev &j, const double *qoi, int which, d
 }
 
 // Chunks per sample of k_qoi: about 8 workgroups per CU in all, 4 nodes or
-// more per thread. Their sums go to the slab that does not hold the state (AB:
-// the next step overwrites all of it that is ever read).
-hipError_t launch_qoi_scalars(const JobDev &j, int64_t t, double *out, int64_t *flag, hipStream_t s) {
+// more per thread. Their sums go to part (QOI_PARTS values), or if that is null
+// to the slab that does not hold the state (AB: the next step overwrites all of
+// it that is ever read).
+hipError_t launch_qoi_scalars(const JobDev &j, int64_t t, double *out, int64_t *flag, double *part, hipStream_t s) {
     const int64_t cells = (int64_t)j.nx * j.ny;
     const int64_t slab2 = j.plane * (j.prec == UQ_FP64 ? 72 : (j.prec == UQ_FP32 ? 36 : 18));  // bytes a sample
     int64_t chunks = 1;
-    double *part = nullptr;
     if (j.layout == UQ_LAYOUT_AB) {
-        part = (double *)((t & 1) ? j.f : j.f2);
-        chunks = std::min<int64_t>(std::min<int64_t>(2048 / j.S, (cells + 1023) / 1024), slab2 / (QOI_PART * 8));
+        if (!part) part = (double *)((t & 1) ? j.f : j.f2);
+        chunks = std::min<int64_t>(std::min<int64_t>(QOI_CHUNKS / j.S, (cells + 1023) / 1024), slab2 / (QOI_PART * 8));
         chunks = std::max<int64_t>(1, chunks);
     }
     const int per = (int)((cells + chunks - 1) / chunks);

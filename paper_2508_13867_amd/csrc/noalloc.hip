@@ -4,7 +4,8 @@
 // kernels as uq_moments; their intermediates -- the per-sample scalar QoIs,
 // the moment outputs and the non-finite flag -- live in one file-scope
 // device array per GPU instead of buffers the job allocates on its first
-// statistics call.
+// statistics call, and the sums of samples cut into chunks behind them instead
+// of in the job's idle slab.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -22,7 +23,7 @@ constexpr int kMaxDevices = 64;
 // Each GPU the library runs on holds its own copy of this array until the
 // process ends. Host code names it only in hipGetSymbolAddress: on the host
 // the name is a stand-in, not a device address.
-__device__ __align__(256) unsigned char scratch[kScratchBytes];
+__device__ __align__(256) unsigned char scratch[kScratchBytes + sizeof(double) * QOI_PARTS];
 
 struct DeviceScratch {
     std::mutex use;       // calls on one device share the array: one at a time
@@ -88,5 +89,6 @@ extern "C" uq_status uq_moments_noalloc(uq_job *j, int32_t qoi, uq_moments_out *
     }
     StatBufs b;
     carve(*j, qoi, (unsigned char *)ds.ptr, &b);
+    b.part = (double *)((unsigned char *)ds.ptr + kScratchBytes);
     return j->moments_in(b, qoi, out);
 }

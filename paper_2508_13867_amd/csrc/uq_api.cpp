@@ -459,7 +459,7 @@ uq_status Job::sample_values_in(const StatBufs &b, int qoi, const double **M, in
     if (qoi_width(P, qoi) == 0) return fail(UQ_EINVAL, "unknown QoI");
     if ((qoi == UQ_QOI_CD || qoi == UQ_QOI_CL) && (P.geometry != UQ_GEOM_CHANNEL || (P.D <= 0 && P.cyl_bc != UQ_CYL_BOUZIDI)))
         return fail(UQ_EINVAL, "drag/lift need a channel with a cylinder");
-    UQ_HIP_TRY(launch_qoi_scalars(jd, t, b.qoi, b.flag, stream));
+    UQ_HIP_TRY(launch_qoi_scalars(jd, t, b.qoi, b.flag, b.part, stream));
     if (qoi_width(P, qoi) == 1) {
         UQ_HIP_TRY(launch_select_scalar(jd, b.qoi, qoi, b.M, stream));
         *M = b.M;
@@ -511,7 +511,7 @@ uq_status Job::moments_in(const StatBufs &b, int qoi, uq_moments_out *out) {
         if (out->var_alt) out->var_alt[0] = h[2];
         if (out->coeffs && K > 0) std::memcpy(out->coeffs, h.data() + 3, sizeof(double) * K);
     } else {
-        UQ_HIP_TRY(launch_qoi_scalars(jd, t, b.qoi, b.flag, stream));
+        UQ_HIP_TRY(launch_qoi_scalars(jd, t, b.qoi, b.flag, b.part, stream));
         UQ_HIP_TRY(launch_field_moments(jd, t, qoi, d_wphi, d_a, K, d_coef, d_mean, d_var, d_alt, stream));
         st = check_finite(b);
         if (st != UQ_OK) return st;

@@ -199,8 +199,11 @@ void tile_counts(const JobDev &j, int cpt, int *tiles_x, int *tiles_y);
 // *d_t += n (one thread; keeps the device copy of the step count current)
 hipError_t launch_advance(int64_t *d_t, int64_t n, hipStream_t s);
 // per-sample scalar QoIs at time t: out[S][4] = {KE, Fx, Fy, nonfinite}, and
-// flag[0] = the first sample with a non-finite value, or S if none
-hipError_t launch_qoi_scalars(const JobDev &j, int64_t t, double *out, int64_t *flag, hipStream_t s);
+// flag[0] = the first sample with a non-finite value, or S if none. Samples cut
+// into chunks leave their sums in part[QOI_PARTS] (null: in the AB layout's idle
+// slab).
+constexpr int QOI_PART = 7, QOI_CHUNKS = 2048, QOI_PARTS = QOI_PART * QOI_CHUNKS;
+hipError_t launch_qoi_scalars(const JobDev &j, int64_t t, double *out, int64_t *flag, double *part, hipStream_t s);
 // M[s] = KE, C_D or C_L of sample s from the scalars above
 hipError_t launch_select_scalar(const JobDev &j, const double *qoi, int which, double *M, hipStream_t s);
 // per-sample fields at time t: out[S][4][ny][nx] = {ux, uy, rho, |u|}

@@ -43,9 +43,10 @@ bool tuned_shape(const uq_problem &p, int64_t S, StepShape *out);
 // and its allocation-free variant): per-sample scalar QoIs qoi[S][4], the
 // selected scalar M[S], per-sample fields fields[S][4][ny][nx] (per-sample
 // field values only; the moments of a field are formed from the populations
-// without them), the outputs out[(K + 3) n_out] and one int64 flag.
+// without them), the outputs out[(K + 3) n_out], one int64 flag and the sums of
+// samples cut into chunks, part[QOI_PARTS] (null: in the job's idle slab).
 struct StatBufs {
-    double *qoi = nullptr, *M = nullptr, *fields = nullptr, *out = nullptr;
+    double *qoi = nullptr, *M = nullptr, *fields = nullptr, *out = nullptr, *part = nullptr;
     int64_t *flag = nullptr;
 };
 
