@@ -246,8 +246,9 @@ static bool default_pipeline(const uq_problem &p, int64_t S, StepShape *s) {
     const int64_t b = storage_bytes(p.precision), slab = S * 9 * plane * b;
     if (9 * plane * b >= ((int64_t)1 << 31) || (channel && plane * 4 >= ((int64_t)1 << 31))) return false;
     if (pipeline_shape(p, S, s) >= single_step_us(p, S)) return false;
-    // A second slab of any size must not be what later jobs miss: it is taken
-    // while a quarter of the card stays free beside both.
+    // The second slab is given back when the library misses it (reclaim_slab);
+    // of what others on the card may miss, a quarter of it stays free beside
+    // both slabs. (Memory that a caller's allocator keeps cached counts as taken.)
     if (slab > ((int64_t)256 << 20)) {
         size_t free_b = 0, total_b = 0;
         if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
@@ -311,6 +312,12 @@ StepShape choose_shape(const uq_problem &p, int64_t S, bool pipelines) {
 // The job's own stream is non-blocking, so it is ordered against the
 // caller's stream explicitly, also when that is the null stream.
 uq_status Job::enter() {
+    if (spare && user_stream) {
+        // a graph that the caller captures names the slabs of now
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(user_stream, &st) != hipSuccess) (void)hipGetLastError();
+        if (st != hipStreamCaptureStatusNone) keep_slabs();
+    }
     if (user_stream != stream) {
         UQ_HIP_TRY(hipEventRecord(ev_in, user_stream));
         UQ_HIP_TRY(hipStreamWaitEvent(stream, ev_in, 0));

@@ -347,6 +347,37 @@ __global__ __launch_bounds__(256) void k_init(JobDev j) {
     }
 }
 
+// The state at step t of an AB job, in the AA layout of that step, in the other
+// slab: bit copies of the stored values. Even t: every node its pulls (a pull
+// beyond an open column brings whatever lies there, as in the gather: its rule
+// overwrites it); odd t: f*_i(x, t-1) in slot opp(i). Once per job at most, for
+// memory that something else needs more; one pass over both slabs.
+template <typename T>
+__global__ __launch_bounds__(256) void k_to_aa(JobDev j, const T *src_all, T *dst_all, int odd) {
+    const int64_t cells = (int64_t)j.ny * j.nx;
+    for (int64_t smp = blockIdx.y; smp < j.S; smp += gridDim.y) {
+        const T *src = src_all + smp * 9 * j.plane;
+        T *dst = dst_all + smp * 9 * j.plane;
+        for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < cells;
+             c += (int64_t)gridDim.x * blockDim.x) {
+            const int y = (int)(c / j.nx), x = (int)(c - (int64_t)y * j.nx);
+            const Site s = site(j, x, y);
+            const int64_t own = (int64_t)y * j.pitch + x;
+            const uint32_t m = j.geom == 1 ? j.mask[own] : 0u;
+#pragma unroll
+            for (int i = 0; i < 9; ++i) {
+                if (odd) {
+                    dst[OPPd[i] * j.plane + own] = src[i * j.plane + own];
+                } else {
+                    const bool bb = (m >> (M_BB + i)) & 1u;
+                    const int64_t from = (int64_t)sy_of(s, -CYd[i]) * j.pitch + sx_of(s, -CXd[i]);
+                    dst[i * j.plane + own] = src[bb ? OPPd[i] * j.plane + own : i * j.plane + from];
+                }
+            }
+        }
+    }
+}
+
 // ------------------------------------------------------------------ QoIs
 // Neumaier's compensated sum
 struct NSum {
@@ -886,6 +917,18 @@ hipError_t launch_init(const JobDev &j, hipStream_t s) {
             else k_init<UQ_BF16S, UQ_LAYOUT_AA><<<grid, 256, 0, s>>>(j);
             break;
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_to_aa(const JobDev &j, int64_t t, hipStream_t s) {
+    const int64_t cells = (int64_t)j.ny * j.nx;
+    dim3 grid((unsigned)std::min<int64_t>((cells + 255) / 256, 1024), (unsigned)std::min<int64_t>(j.S, 65535));
+    const int odd = (int)(t & 1);
+    const void *src = odd ? j.f2 : j.f;
+    void *dst = odd ? j.f : j.f2;
+    if (j.prec == UQ_FP64) k_to_aa<<<grid, 256, 0, s>>>(j, (const uint64_t *)src, (uint64_t *)dst, odd);
+    else if (j.prec == UQ_FP32) k_to_aa<<<grid, 256, 0, s>>>(j, (const uint32_t *)src, (uint32_t *)dst, odd);
+    else k_to_aa<<<grid, 256, 0, s>>>(j, (const uint16_t *)src, (uint16_t *)dst, odd);
     return hipGetLastError();
 }
 

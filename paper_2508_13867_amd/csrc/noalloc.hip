@@ -75,6 +75,7 @@ extern "C" uq_status uq_moments_noalloc(uq_job *j, int32_t qoi, uq_moments_out *
         return fail(UQ_EINVAL, "uq_moments_noalloc: this QoI of this job needs " + std::to_string(need) +
                                    " B of scratch, more than the library's fixed " + std::to_string(kScratchBytes) +
                                    " B (use uq_moments)");
+    std::lock_guard<std::recursive_mutex> job(j->mu);
     UQ_HIP_TRY(hipSetDevice(dev));
     DeviceScratch &ds = g_dev[dev];
     // held until the results are on the host: the next call may then reuse

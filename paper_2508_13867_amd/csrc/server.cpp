@@ -39,12 +39,14 @@ class Arena {
     uq_status init(size_t bytes, const uq_device &dev) {
         cap_ = (bytes + 255) / 256 * 256;
         dev_ = dev;
-        if (dev_.alloc) {
-            base_ = (char *)dev_.alloc(cap_, dev_.ctx);
-        } else if (hipMalloc(&base_, cap_) != hipSuccess) {
-            (void)hipGetLastError();
-            base_ = nullptr;
-        }
+        do {
+            if (dev_.alloc) {
+                base_ = (char *)dev_.alloc(cap_, dev_.ctx);
+            } else if (hipMalloc(&base_, cap_) != hipSuccess) {
+                (void)hipGetLastError();
+                base_ = nullptr;
+            }
+        } while (!base_ && reclaim_slab(dev_.device));
         if (!base_) return fail(UQ_ENOMEM, "server arena of " + std::to_string(cap_) + " B does not fit on the device");
         free_[0] = cap_;
         return UQ_OK;
@@ -363,7 +365,7 @@ void Server::admit() {
             sh.layout = UQ_LAYOUT_AA;
         }
         uq_job *j = nullptr;
-        uq_status st = create_job(r.p, &dv, &sh, &j);
+        uq_status st = create_job(r.p, &dv, &sh, &j, false);
         if (st == UQ_ENOMEM) {  // fragmentation: retry when memory frees up
             std::lock_guard<std::mutex> lk(mu);
             pending.push_front(r);

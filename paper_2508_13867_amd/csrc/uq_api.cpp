@@ -5,10 +5,13 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
+#include <condition_variable>
 #include <cstdlib>
 #include <cstring>
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -18,7 +21,102 @@
 namespace uqi {
 
 // ------------------------------------------------------------------ device memory
+// Jobs that hold a second slab which they took on their own account, and how many
+// such slabs are held outside the register: of jobs being made or destroyed, or
+// on their way back to their allocator.
+static std::mutex g_spare_mu;
+static std::condition_variable g_spare_cv;
+static std::vector<Job *> g_spare;
+static int g_transit = 0;
+static thread_local int t_transit = 0;  // this thread's share
+
+InTransit::InTransit(bool counts) : on(counts) {
+    if (!on) return;
+    std::lock_guard<std::mutex> lk(g_spare_mu);
+    ++g_transit;
+    ++t_transit;
+}
+InTransit::~InTransit() {
+    if (!on) return;
+    {
+        std::lock_guard<std::mutex> lk(g_spare_mu);
+        --g_transit;
+        --t_transit;
+    }
+    g_spare_cv.notify_all();
+}
+
+// Such a slab only makes steps faster; what a caller asks for comes first. So an
+// allocation that fails takes them back, one job at a time: the state goes into
+// the AA layout and the job runs on in one slab, with the same results. A job
+// whose call is running on another thread is waited for: that call ends, or
+// comes here itself and starts with its own slab (the calling thread's own jobs
+// are taken too: an allocation is no place where a call relies on the layout).
+// The register's lock is held only to pick a job, and no callback of a caller's
+// runs under either lock: one may well destroy the job.
+bool reclaim_slab(int device) {
+    std::unique_lock<std::mutex> lk(g_spare_mu);
+    for (bool waited = false;; waited = true) {
+        bool busy = false;
+        for (size_t i = 0; i < g_spare.size(); ++i) {
+            Job *q = g_spare[i];
+            if (q->dev.device != device) continue;
+            if (!q->mu.try_lock()) {
+                busy = true;
+                continue;
+            }
+            std::unique_lock<std::recursive_mutex> job(q->mu, std::adopt_lock);
+            g_spare.erase(g_spare.begin() + (long)i);
+            q->spare = false;
+            ++g_transit;
+            ++t_transit;
+            lk.unlock();
+            InTransit moving(std::adopt_lock);
+            const uq_device dev = q->dev;
+            void *slab = q->to_one_slab();
+            job.unlock();
+            if (slab && dev.alloc)
+                dev.free(slab, dev.ctx);
+            else if (slab)
+                (void)hipFree(slab);
+            return true;
+        }
+        if (!busy && g_transit == t_transit) return waited;  // (what was on its way has arrived)
+        g_spare_cv.wait_for(lk, std::chrono::milliseconds(1));
+    }
+}
+
+// (q->mu held.) Null, and the job as it was, if the device reports an error.
+void *Job::to_one_slab() {
+    if (hipSetDevice(dev.device) != hipSuccess || hipStreamSynchronize(stream) != hipSuccess ||
+        launch_to_aa(jd, t, stream) != hipSuccess || hipStreamSynchronize(stream) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    release_graph();  // it names both slabs
+    void *old = (t & 1) ? jd.f2 : jd.f;
+    jd.f = (t & 1) ? jd.f : jd.f2;
+    jd.f2 = nullptr;
+    jd.layout = UQ_LAYOUT_AA;
+    shape = StepShape();
+    allocs.erase(std::find(allocs.begin(), allocs.end(), old));
+    bytes_held -= S * 9 * jd.plane * storage_bytes(p.precision);
+    return old;
+}
+
+void Job::keep_slabs() {
+    std::lock_guard<std::mutex> lk(g_spare_mu);
+    spare = false;
+    g_spare.erase(std::remove(g_spare.begin(), g_spare.end(), this), g_spare.end());
+}
+
 void *Job::dalloc(size_t bytes) {
+    void *p = dalloc_now(bytes);
+    while (!p && reclaims && reclaim_slab(dev.device)) p = dalloc_now(bytes);
+    return p;
+}
+
+void *Job::dalloc_now(size_t bytes) {
     if (bytes == 0) bytes = 256;
     void *p = nullptr;
     if (dev.alloc) {
@@ -203,11 +301,14 @@ uq_status Job::own_stat_bufs(int qoi, bool fields, StatBufs *b) {
 
 namespace uqi {
 
-uq_status create_job(const uq_problem &prob, const uq_device *dev, const StepShape *forced, uq_job **out) {
+uq_status create_job(const uq_problem &prob, const uq_device *dev, const StepShape *forced, uq_job **out,
+                     bool reclaim) {
     const uq_problem *p = &prob;
     *out = nullptr;
+    std::unique_ptr<InTransit> moving;  // (outlives the job)
     std::unique_ptr<uq_job> j(new uq_job());
     j->p = *p;
+    j->reclaims = reclaim;
     if (dev) j->dev = *dev;
     uq_status st = build_rule(j->p, j->rule);
     if (st != UQ_OK) return st;
@@ -268,32 +369,27 @@ uq_status create_job(const uq_problem &prob, const uq_device *dev, const StepSha
     j->shape = forced ? *forced : choose_shape(P, j->S);
     if (needs_ab(P) && j->shape.layout != UQ_LAYOUT_AB)
         return fail(UQ_EINVAL, "interpolated boundaries need the AB layout");
+    // A second slab that a pipeline would like, but nobody asked for, is taken
+    // last and without asking others for theirs; without it the job keeps to one.
+    StepShape one;
+    bool spare = false;
+    if (!forced && P.layout == UQ_LAYOUT_AUTO && j->shape.layout == UQ_LAYOUT_AB) {
+        one = choose_shape(P, j->S, false);
+        spare = one.layout != UQ_LAYOUT_AB && one.pad == j->shape.pad;
+    }
     // padding after each population plane (elements, multiple of 64): spreads
     // the nine plane streams of a wavefront over HBM channels
-    auto slabs = [&](void **slab, void **slab2) {
-        const int64_t pad = std::max(0, j->shape.pad) / 64 * 64;
-        const int64_t plane = (int64_t)P.ny * j->pitch + pad;
-        const size_t bytes = (size_t)(j->S * 9 * plane * storage_bytes(P.precision));
-        *slab = j->dalloc(bytes);
-        *slab2 = *slab && j->shape.layout == UQ_LAYOUT_AB ? j->dalloc(bytes) : nullptr;
-    };
-    void *slab = nullptr, *slab2 = nullptr;
-    slabs(&slab, &slab2);
-    if (j->shape.layout == UQ_LAYOUT_AB && !slab2 && !forced && P.layout == UQ_LAYOUT_AUTO) {
-        // no room for the second slab that a pipeline would have liked
-        const StepShape one = choose_shape(P, j->S, false);
-        if (one.layout != UQ_LAYOUT_AB) {
-            j->dfree_all();
-            j->shape = one;
-            slabs(&slab, &slab2);
-        }
-    }
     const int64_t pad = std::max(0, j->shape.pad) / 64 * 64;
     const int64_t plane = (int64_t)P.ny * j->pitch + pad;
     const int64_t slab_bytes = j->S * 9 * plane * storage_bytes(P.precision);
-    if (slab && j->shape.layout == UQ_LAYOUT_AB && !slab2) {
-        j->dfree_all();
-        return fail(UQ_ENOMEM, "out of device memory for the second slab (" + std::to_string(slab_bytes) + " B)");
+    void *slab = j->dalloc((size_t)slab_bytes);
+    void *slab2 = nullptr;
+    if (slab && j->shape.layout == UQ_LAYOUT_AB && !spare) {
+        slab2 = j->dalloc((size_t)slab_bytes);
+        if (!slab2) {
+            j->dfree_all();
+            return fail(UQ_ENOMEM, "out of device memory for the second slab (" + std::to_string(slab_bytes) + " B)");
+        }
     }
     SampleDev *d_smp = (SampleDev *)j->dalloc(sizeof(SampleDev) * j->S);
     j->d_t = (int64_t *)j->dalloc(sizeof(int64_t));
@@ -327,6 +423,15 @@ uq_status create_job(const uq_problem &prob, const uq_device *dev, const StepSha
         UQ_HIP_TRY(hipMemcpyAsync(j->d_wphi, wphi.data(), sizeof(double) * wphi.size(), hipMemcpyHostToDevice, j->stream));
         UQ_HIP_TRY(hipMemcpyAsync(j->d_a, j->rule.a.data(), sizeof(double) * j->S, hipMemcpyHostToDevice, j->stream));
         UQ_HIP_TRY(hipStreamSynchronize(j->stream));
+    }
+    if (spare) {
+        moving.reset(new InTransit(true));
+        slab2 = j->dalloc_now((size_t)slab_bytes);
+        if (!slab2) {
+            j->shape = one;
+            spare = false;
+            moving.reset();
+        }
     }
     const int64_t zero = 0;
     UQ_HIP_TRY(hipMemcpyAsync(j->d_t, &zero, sizeof(int64_t), hipMemcpyHostToDevice, j->stream));
@@ -374,6 +479,11 @@ uq_status create_job(const uq_problem &prob, const uq_device *dev, const StepSha
         uq_status e = j->leave();
         if (e != UQ_OK) return e;
     }
+    if (spare) {
+        std::lock_guard<std::mutex> lk(g_spare_mu);
+        j->spare = true;
+        g_spare.push_back(j.get());
+    }
     *out = j.release();
     return UQ_OK;
 }
@@ -399,6 +509,7 @@ extern "C" uq_status uq_samples(const uq_job *j, double *xi, double *a, int64_t 
 extern "C" uq_status uq_run(uq_job *j, int64_t steps) {
     if (!j) return fail(UQ_EINVAL, "null job");
     if (steps < 0) return fail(UQ_EINVAL, "steps must be >= 0");
+    std::lock_guard<std::recursive_mutex> lk(j->mu);
     UQ_HIP_TRY(hipSetDevice(j->dev.device));
     uq_status st = j->enter();
     if (st != UQ_OK) return st;
@@ -410,6 +521,7 @@ extern "C" uq_status uq_run(uq_job *j, int64_t steps) {
 extern "C" uq_status uq_run_timed(uq_job *j, int64_t steps, double *ms) {
     if (!j || !ms) return fail(UQ_EINVAL, "null argument");
     if (steps < 0) return fail(UQ_EINVAL, "steps must be >= 0");
+    std::lock_guard<std::recursive_mutex> lk(j->mu);
     UQ_HIP_TRY(hipSetDevice(j->dev.device));
     uq_status st = j->enter();
     if (st != UQ_OK) return st;
@@ -534,6 +646,7 @@ uq_status Job::moments_in(const StatBufs &b, int qoi, uq_moments_out *out) {
 
 extern "C" uq_status uq_qoi_samples(uq_job *j, int32_t qoi, double *out, int64_t *n_out) {
     if (!j) return fail(UQ_EINVAL, "null job");
+    std::lock_guard<std::recursive_mutex> lk(j->mu);
     UQ_HIP_TRY(hipSetDevice(j->dev.device));
     int64_t n = qoi_width(j->p, qoi);
     if (n == 0) return fail(UQ_EINVAL, "unknown QoI");
@@ -553,6 +666,7 @@ extern "C" uq_status uq_qoi_samples(uq_job *j, int32_t qoi, double *out, int64_t
 
 extern "C" uq_status uq_moments(uq_job *j, int32_t qoi, uq_moments_out *out) {
     if (!j || !out) return fail(UQ_EINVAL, "null argument");
+    std::lock_guard<std::recursive_mutex> lk(j->mu);
     UQ_HIP_TRY(hipSetDevice(j->dev.device));
     if (qoi_width(j->p, qoi) == 0) return fail(UQ_EINVAL, "unknown QoI");
     StatBufs b;
@@ -564,6 +678,7 @@ extern "C" uq_status uq_moments(uq_job *j, int32_t qoi, uq_moments_out *out) {
 extern "C" uq_status uq_populations(uq_job *j, int64_t sample, double *out) {
     if (!j || !out) return fail(UQ_EINVAL, "null argument");
     if (sample < 0 || sample >= j->S) return fail(UQ_EINVAL, "sample out of range");
+    std::lock_guard<std::recursive_mutex> lk(j->mu);
     UQ_HIP_TRY(hipSetDevice(j->dev.device));
     const int64_t cells = (int64_t)j->p.nx * j->p.ny;
     if (!j->d_export) {
@@ -580,6 +695,7 @@ extern "C" uq_status uq_populations(uq_job *j, int64_t sample, double *out) {
 
 extern "C" uq_status uq_job_get_info(const uq_job *j, uq_job_info *info) {
     if (!j || !info) return fail(UQ_EINVAL, "null argument");
+    std::lock_guard<std::recursive_mutex> lk(j->mu);
     info->S = j->S;
     info->d = j->rule.d;
     info->K = j->K;
@@ -602,6 +718,10 @@ extern "C" uq_status uq_job_get_info(const uq_job *j, uq_job_info *info) {
 
 extern "C" void uq_destroy(uq_job *j) {
     if (!j) return;
+    j->mu.lock();
+    InTransit moving(j->spare);
+    j->keep_slabs();  // nobody takes one any more
+    j->mu.unlock();
     (void)hipSetDevice(j->dev.device);
     delete j;  // waits for the job stream, then releases graph, buffers, stream
 }

@@ -153,6 +153,9 @@ struct StepShape {
 hipError_t launch_init(const JobDev &j, hipStream_t s);
 hipError_t launch_step(const JobDev &j, const int64_t *d_t, int k, int parity, const StepShape &shape,
                        hipStream_t s);
+// the state at step t of an AB job without interpolated rules, in the AA layout
+// of that step: from the slab of t's parity into the other one
+hipError_t launch_to_aa(const JobDev &j, int64_t t, hipStream_t s);
 // n = 2..4 fused steps of a periodic AB job in one launch: the state is
 // read from slab f2 if src2 else f and n steps later written to the other
 // slab (the host keeps the slab of each step's state; see Job::enqueue_steps)

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <mutex>
 #include <vector>
 
 #include "uq_internal.h"
@@ -78,6 +79,13 @@ struct Job {
 
     std::vector<void *> allocs;
     int64_t bytes_held = 0;
+    // A second slab that the job took on its own account (nobody asked for the
+    // AB layout) is given back when memory runs out: see reclaim_slab. `mu` is
+    // held by every call on the job, and by another job's call while it takes
+    // the slab.
+    bool spare = false;    // holds such a slab (and is in the register)
+    bool reclaims = true;  // its own allocations may ask others for theirs
+    mutable std::recursive_mutex mu;
     double *d_qoi = nullptr, *d_M = nullptr, *d_out = nullptr, *d_fields = nullptr;
     double *d_wphi = nullptr, *d_a = nullptr, *d_export = nullptr;
     int64_t *d_flag = nullptr;
@@ -91,7 +99,10 @@ struct Job {
 
     ~Job();
     void *dalloc(size_t bytes);
-    void dfree(void *p);  // release one block from dalloc
+    void *dalloc_now(size_t bytes);  // without asking other jobs for memory
+    void dfree(void *p);             // release one block from dalloc
+    void *to_one_slab();             // AB to AA; the slab that is no longer needed (null: could not)
+    void keep_slabs();               // out of the register
     void dfree_all();
     uq_status ensure_stats_buffers(int64_t n_out_max);
     uq_status ensure_fields();
@@ -117,6 +128,21 @@ struct Job {
 struct uq_job : public uqi::Job {};
 
 namespace uqi {
-// Build a job; `forced` (may be null) fixes layout and launch shape.
-uq_status create_job(const uq_problem &p, const uq_device *dev, const StepShape *forced, uq_job **out);
+// Build a job; `forced` (may be null) fixes layout and launch shape. reclaim =
+// false: its memory is a pool of the library's own, which other jobs' slabs do
+// not fill.
+uq_status create_job(const uq_problem &p, const uq_device *dev, const StepShape *forced, uq_job **out,
+                     bool reclaim = true);
+// One job on the device gives back the second slab that it took on its own
+// account. False if there is none to wait for.
+bool reclaim_slab(int device);
+// While one is alive such a slab is held by a job outside the register.
+struct InTransit {
+    const bool on;
+    explicit InTransit(bool counts);
+    explicit InTransit(std::adopt_lock_t) : on(true) {}  // (counted already)
+    ~InTransit();
+    InTransit(const InTransit &) = delete;
+    InTransit &operator=(const InTransit &) = delete;
+};
 }  // namespace uqi

@@ -176,6 +176,7 @@ extern "C" uq_status uq_wasserstein1(uq_job *a, uq_job *b, int32_t qoi, double s
     for (Job *j : {(Job *)a, (Job *)b})
         for (double w : j->rule.a)
             if (w < 0.0) return fail(UQ_EINVAL, "W1 needs a rule with nonnegative weights");
+    std::scoped_lock both(a->mu, b->mu);  // (once each for two jobs, twice for one)
     UQ_HIP_TRY(hipSetDevice(a->dev.device));
     uq_status st = a->enter();
     if (st != UQ_OK) return st;

@@ -1,0 +1,212 @@
+"""The second slab that an untuned job takes on its own account must not be what
+the library misses: every set of jobs and calls that fits with one slab each
+fits with the defaults. The device's memory is played by an allocator with a
+budget; results stay bit for bit those of one slab from the start."""
+import threading
+
+import numpy as np
+import pytest
+
+VORTEX = dict(geometry="tgv", nx=96, ny=64, u0=0.03, nu=0.02, dists=[("nu", 0.015, 0.025), ("u0", 0.02, 0.04)],
+              rule=dict(kind="gl", n=4, order=1))
+CHANNEL = dict(geometry="channel", nx=130, ny=41, u_peak=0.05, nu=0.05, D=10, cx=30, cy=18, ramp=20, xbc="zouhe",
+               dists=[("re", 16.0, 24.0), ("u_peak", 0.045, 0.055)], rule=dict(kind="gl", n=4, order=1))
+STORED = dict(fp64=8, fp32=4, fp16s=2, bf16s=2)
+
+
+def slab(spec):
+    return 16 * 9 * (spec["ny"] * -(-spec["nx"] // 64) * 64 + 64) * STORED[spec["precision"]]
+
+
+@pytest.fixture
+def budget(monkeypatch):
+    """budget(bytes): what all jobs created from then on have together."""
+    from paper_2508_13867_amd import _abi as A
+
+    state = dict(free=1 << 40, lock=threading.Lock())
+
+    class Budget(A.TorchAllocator):
+        def alloc(self, nbytes, ctx):
+            with state["lock"]:
+                if nbytes > state["free"]:
+                    return None
+                state["free"] -= nbytes
+            return super().alloc(nbytes, ctx)
+
+        def free(self, ptr, ctx):
+            with state["lock"]:
+                state["free"] += self.live[ptr].numel()
+            super().free(ptr, ctx)
+
+    monkeypatch.setattr(A, "TorchAllocator", Budget)
+    for k in ("UQ_FUSE", "UQ_FUSE_TY", "UQ_FUSE_WINDOW", "UQ_LAYOUT", "UQ_CPT", "UQ_BX", "UQ_PLANE_PAD"):
+        monkeypatch.delenv(k, raising=False)
+
+    def start(nbytes):
+        state["free"] = int(nbytes)
+        return state
+
+    return start
+
+
+def populations(job):
+    return np.stack([job.populations(s) for s in (0, 7, 15)])
+
+
+def one_slab(spec, *steps):
+    from paper_2508_13867_amd import Job
+
+    out = []
+    with Job(dict(spec, layout="aa")) as job:
+        for n in steps:
+            job.run(n)
+            out.append(populations(job))
+    return out
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("steps", [0, 1, 24, 25, 130])
+@pytest.mark.parametrize("spec", [dict(VORTEX, precision="fp64"), dict(VORTEX, precision="fp32"),
+                                  dict(VORTEX, precision="fp16s"), dict(VORTEX, precision="bf16s"),
+                                  dict(CHANNEL, precision="fp32"), dict(CHANNEL, precision="fp64"),
+                                  dict(CHANNEL, precision="fp16s", nx=100)],
+                         ids=lambda s: f"{s['geometry']}-{s['precision']}")
+def test_a_job_that_fits_beside_one_slab(spec, steps, budget):
+    from paper_2508_13867_amd import Job
+
+    print("case second slab", spec["geometry"], spec["precision"], steps, flush=True)
+    want = one_slab(spec, steps, 37)
+    budget(2.3 * slab(spec) + (600 << 10))
+    with Job(spec) as a:
+        took_two = a.info().layout == 2
+        held = a.info().device_bytes
+        a.run(steps)
+        with Job(dict(spec, layout="aa")) as b:
+            b.run(3)
+            assert a.info().layout == 1 and not a.info().fused
+            assert took_two == (a.info().device_bytes == held - slab(spec))
+            assert np.array_equal(populations(a), want[0])
+            a.run(37)
+            assert np.array_equal(populations(a), want[1])
+        assert took_two or spec["geometry"] == "channel"
+
+
+@pytest.mark.gpu
+def test_two_untuned_jobs(budget):
+    from paper_2508_13867_amd import Job
+
+    print("case two untuned jobs", flush=True)
+    spec = dict(VORTEX, precision="fp32")
+    budget(2.3 * slab(spec) + (600 << 10))
+    with Job(spec) as a, Job(spec) as b:
+        # b got its one slab; it does not take a's place for a second
+        assert sorted([a.info().layout, b.info().layout]) == [1, 1]
+        a.run(20)
+        b.run(20)
+        assert np.array_equal(populations(a), populations(b))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("steps", [24, 25])
+def test_the_jobs_own_statistics(steps, budget):
+    from paper_2508_13867_amd import Job, wasserstein1
+
+    print("case own statistics", steps, flush=True)
+    spec = dict(VORTEX, precision="fp32")
+    cells = 96 * 64
+    fields = 16 * 4 * cells * 8
+    with Job(dict(spec, layout="aa")) as job:
+        job.run(steps)
+        want = job.qoi_samples("vel")
+    budget(slab(spec) + fields + (2 << 20))
+    with Job(spec) as job:
+        assert job.info().layout == 2
+        job.run(steps)
+        assert np.array_equal(job.qoi_samples("vel"), want)
+        assert job.info().layout == 1
+    # W_1 sorts in memory taken through job a while b holds two slabs as well
+    budget(1 << 40)
+    with Job(dict(spec, layout="aa")) as a, Job(dict(spec, layout="aa", nu=0.02, u0=0.031)) as b:
+        a.run(steps)
+        b.run(steps + 8)
+        w = wasserstein1(a, b, "speed")
+    budget(2 * (slab(spec) + fields) + 6 * 16 * cells * 8 + (4 << 20))
+    with Job(spec) as a, Job(dict(spec, nu=0.02, u0=0.031)) as b:
+        assert a.info().layout == b.info().layout == 2
+        a.run(steps)
+        b.run(steps + 8)
+        # (the weights' prefix sums depend on the scan's timing)
+        assert wasserstein1(a, b, "speed") == pytest.approx(w, rel=1e-12)
+        assert 1 in (a.info().layout, b.info().layout)
+
+
+@pytest.mark.gpu
+def test_a_server_started_beside_jobs(budget):
+    from paper_2508_13867_amd import Job, Server
+
+    print("case server beside jobs", flush=True)
+    spec = dict(VORTEX, precision="fp32", ny=640)
+    want = one_slab(spec, 9)[0]
+    budget(2 * slab(spec) + (1 << 20))
+    with Job(spec) as job:
+        assert job.info().layout == 2
+        job.run(9)
+        with Server(memory_budget_gb=30 / 1024, max_jobs=4, steps_per_tick=48, precision="fp32") as srv:
+            assert job.info().layout == 1
+            assert srv.wait(srv.submit(dict(spec, ny=64), 60, "ke"))["status"] == 0
+        assert np.array_equal(populations(job), want)
+
+
+@pytest.mark.gpu
+def test_threads_that_take_each_others_slabs(budget):
+    from paper_2508_13867_amd import Job
+
+    print("case threads", flush=True)
+    specs = [dict(VORTEX, precision="fp32"), dict(CHANNEL, precision="fp32"), dict(VORTEX, precision="fp64", nx=48),
+             dict(VORTEX, precision="fp16s", ny=90)]
+    want = [one_slab(s, 20, 31) for s in specs]
+    one = sum(slab(s) for s in specs)
+    budget(1.1 * one + (2 << 20))
+    errs = []
+
+    def work(k):
+        try:
+            for _ in range(6):
+                with Job(specs[k]) as job:
+                    for n, w in zip((20, 31), want[k]):
+                        job.run(n)
+                        assert np.array_equal(populations(job), w)
+        except BaseException as e:  # noqa: BLE001
+            errs.append((k, e))
+
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    [t.start() for t in ts]
+    [t.join(100) for t in ts]
+    assert not errs, errs
+
+
+@pytest.mark.gpu
+def test_a_captured_job_keeps_its_slabs(budget):
+    import torch
+
+    from paper_2508_13867_amd import Job, UQError
+
+    print("case captured job", flush=True)
+    spec = dict(VORTEX, precision="fp32")
+    want = one_slab(spec, 24 * 4)[0]
+    budget(2.3 * slab(spec) + (600 << 10))
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s), Job(spec, stream=s) as job:
+        assert job.info().layout == 2
+        job.run(24)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s, capture_error_mode="thread_local"):
+            job.run(24)  # whole launch pairs: the graph can be replayed
+        with pytest.raises(UQError):  # its graph names both slabs
+            Job(dict(spec, layout="aa"))
+        assert job.info().layout == 2
+        for _ in range(3):
+            graph.replay()
+            torch.cuda.synchronize()
+        assert np.array_equal(populations(job), want)
