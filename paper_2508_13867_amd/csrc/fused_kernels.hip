@@ -1233,8 +1233,8 @@ __global__ __launch_bounds__(64 * N, 2) void k_stepRCS(
 
 // Batched form (see k_stepRC_multi)
 template <int P, int N, int D>
-__global__ __launch_bounds__(64 * N, 2) void k_stepRCS_multi(const FusedJob *jobs, int njobs,
-                                                                                  int64_t nwork, int launch) {
+__global__ __launch_bounds__(64 * N, 2) void k_stepRCS_multi(const FusedJob *jobs, int njobs, int64_t nwork,
+                                                             int launch) {
     __shared__ RowsRingCS<P, N> rg;
     const int64_t G = gridDim.x;
     for (int64_t wk = xcd_logical(blockIdx.x, G); wk < nwork; wk += G) {
@@ -1322,6 +1322,7 @@ __global__ __launch_bounds__(TILE_NODES) void k_stepT(JobDev j, bool src2, int n
         __syncthreads();  // both buffers are free for the next tile
     }
 }
+
 // ------------------------------------------------------------------ launchers
 template <int P, int N>
 static void stepN_p(const JobDev &j, bool src2, int fty, hipStream_t s) {
@@ -1376,7 +1377,7 @@ static void stepRS_p(const JobDev &j, bool src2, int rows, hipStream_t s) {
 }
 
 // full-row kernel: K waves per level of M columns per lane cover nx, with
-// N K <= 16 waves and (N - 1) 27 LDS rows of 64 K M + 2 values within 160 KB
+// N K <= 16 waves and (N - 1) 21 LDS rows of 64 K M values within 160 KB
 template <int P, int N, int K, int M>
 static void stepR_k(const JobDev &j, bool src2, int rows, bool nt, hipStream_t s) {
     const int H = std::max(8, std::min(rows, j.ny));
@@ -1461,13 +1462,10 @@ bool fused_launch_multi(int kind, int n, int K, int M, const FusedJob *jobs, int
         return true;
     }
     if (kind == 3) {
-        if constexpr (P != UQ_FP64) {
-            if (n != 8) return false;
-            const int64_t G = std::min<int64_t>(nwork, 0x7fffffff);
-            k_stepRCS_multi<P, 8, 2><<<(unsigned)G, 512, 0, s>>>(jobs, njobs, nwork, launch);
-            return true;
-        }
-        return false;
+        if (n != 8) return false;
+        const int64_t G = std::min<int64_t>(nwork, 0x7fffffff);
+        k_stepRCS_multi<P, 8, 2><<<(unsigned)G, 512, 0, s>>>(jobs, njobs, nwork, launch);
+        return true;
     }
     if (kind == 0) {
         if (n == 4) return multi_n<P, 4>(0, K, M, jobs, njobs, nwork, launch, s);
@@ -1527,6 +1525,8 @@ void fused_launch_tgv(const JobDev &j, int n, bool src2, int fty, int window, bo
 
 template void fused_launch_tgv<UQ_PREC>(const JobDev &, int, bool, int, int, bool, hipStream_t);
 template void fused_launch_channel<UQ_PREC>(const JobDev &, int, const int64_t *, int, bool, int, int, hipStream_t);
+#if UQ_PREC != 0  // the server runs double precision (UQ_FP64) in single steps
 template bool fused_launch_multi<UQ_PREC>(int, int, int, int, const FusedJob *, int, int64_t, int, hipStream_t);
+#endif
 
 }  // namespace uqi

@@ -1104,11 +1104,11 @@ bool channel_fusable(const JobDev &j) {
 // ------------------------------------------------------------------ batched fused launches
 // One launch of a batched fused instance (kind 0: periodic rows,
 // k_stepR_multi; kind 1: channel rows, k_stepRC_multi; kind 2: strips of
-// periodic rows, k_stepRS_multi; kind 3: of channel rows, k_stepRCS_multi): every work item of the table's jobs. The
-// server keeps to N in {4, 6, 8} (periodic rows), {2, 3, 4} (channel) and 8
-// (strips)
-// and to single precision storage (FP32, FP16S, BF16S), so that a tick of 48
-// steps holds a whole number of launch pairs of every instance.
+// periodic rows, k_stepRS_multi; kind 3: of channel rows, k_stepRCS_multi):
+// every work item of the table's jobs. The server keeps to N in {4, 6, 8}
+// (periodic rows), {2, 3, 4} (channel) and 8 (strips) and to single precision
+// storage (FP32, FP16S, BF16S), so that a tick of 48 steps holds a whole number
+// of launch pairs of every instance.
 int rows_instance(int kind, int prec, int n, int nx, int *K, int *M) {
     if (kind >= 2) {  // strips: any width
         *K = *M = 0;

@@ -142,10 +142,11 @@ struct StepShape {
     int layout = UQ_LAYOUT_AA;
     int pad = 64;       // elements of padding after each population plane
     int bx = 64;        // workgroup width along x (64, 128 or 256; height 256/bx)
-    int fuse = 0;       // periodic AB jobs: steps per launch of k_stepN (2..4; 0, 1: k_step)
-    int fty = 8;        // k_stepN tile height (rows of 64 output nodes); k_stepW chunk rows
-    int fwin = 0;       // fused kernel: 0 tiles (k_stepN), 1 sliding window (k_stepW), 2 full rows (k_stepR),
-                        // 3 strips of rows (k_stepRS)
+    int fuse = 0;       // AB jobs: steps per launch of the fused kernel (0, 1: k_step)
+    int fty = 8;        // k_stepN tile height (rows of 64 output nodes); chunk rows of the pipelines
+    int fwin = 0;       // fused kernel (steps per launch): 0 tiles (k_stepN, 2..4), 1 sliding window (k_stepW,
+                        // 2..4), 2 full rows (k_stepR 2..8, k_stepRC 2..4), 3 strips of rows (k_stepRS 3..8,
+                        // k_stepRCS 3..8, double precision 3..7), 4 resident tiles (k_stepT, 2..16)
 };
 
 // one stream-collide step for all samples at time t = *d_t + k; `parity`
@@ -156,12 +157,12 @@ hipError_t launch_step(const JobDev &j, const int64_t *d_t, int k, int parity, c
 // the state at step t of an AB job without interpolated rules, in the AA layout
 // of that step: from the slab of t's parity into the other one
 hipError_t launch_to_aa(const JobDev &j, int64_t t, hipStream_t s);
-// n = 2..4 fused steps of a periodic AB job in one launch: the state is
-// read from slab f2 if src2 else f and n steps later written to the other
-// slab (the host keeps the slab of each step's state; see Job::enqueue_steps)
+// n fused steps of an AB job in one launch: the state is read from slab f2 if
+// src2 else f and n steps later written to the other slab (the host keeps the
+// slab of each step's state; see Job::enqueue_steps)
 // (window 1: the sliding-window kernel with chunks of fty rows, its stores
 // non-temporal if nt; 2: the same over whole rows; 3: the whole-row pipeline
-// down strips; 0: the 64 x fty tile kernel)
+// down strips; 4: resident tiles; 0: the 64 x fty tile kernel)
 // (channel jobs: windows 2 and 3, advancing the steps t = *d_t + k ..; see
 // channel_fusable)
 hipError_t launch_fused(const JobDev &j, int n, bool src2, int fty, int window, bool nt, const int64_t *d_t, int k,
@@ -178,8 +179,8 @@ int full_rows_max_nx(int prec, int n);
 bool fused_supported(const JobDev &j);
 // Batched fused launches (continuous batching with temporal blocking).
 // kind 0: periodic lattice over whole rows, kind 1: channel over whole rows,
-// kind 2: periodic lattice in strips of whole-row pipelines (any width).
-// rows_instance gives the waves per level K and columns per lane M
+// kind 2: periodic lattice in strips of whole-row pipelines (any width), kind
+// 3: channel likewise. rows_instance gives the waves per level K and columns per lane M
 // of the N-step whole-row instance for rows nx wide (0 if none fits);
 // fused_multi_supported says whether the batched form of an instance exists
 // (N in {4, 6, 8} periodic rows, {2, 3, 4} channel rows, 8 strips; single-
