@@ -260,6 +260,13 @@ static bool default_pipeline(const uq_problem &p, int64_t S, StepShape *s) {
     return true;
 }
 
+// Stores of single AB steps that bypass the caches pay where two slabs do not fit
+// the 256 MB cache beside HBM; where they do, the next step reads them from it.
+// The paper's 440 x 80 cylinder, us per step with and without: FP64 x 11 (57
+// MB) 19.8, 14.9; FP32 x 32 (83 MB) 23.8, 20.4; FP64 x 32 (165 MB) 37.2,
+// 33.7; FP32 x 100 (258 MB) 63.0, 64.4; FP64 x 100 (516 MB) 105, 121.
+static bool stores_bypass(int64_t slab_bytes) { return 2 * slab_bytes > ((int64_t)200 << 20); }
+
 // Launch shape and layout of a job. Order of precedence: a shape measured by
 // uq_autotune for this problem class (when the problem leaves the layout to
 // AUTO, or fixes the same layout), then the UQ_* environment overrides, then
@@ -296,16 +303,9 @@ StepShape choose_shape(const uq_problem &p, int64_t S, bool pipelines) {
         if (v && (v[0] == 'a' || v[0] == 'A') && (v[1] == 'b' || v[1] == 'B')) s.layout = UQ_LAYOUT_AB;
     }
     if (needs_ab(p)) s.layout = UQ_LAYOUT_AB;
-    // Stores that bypass the caches pay where two slabs do not fit the 256 MB
-    // cache beside HBM; where they do, the next step reads them from it. The
-    // paper's 440 x 80 cylinder, us per step with and without: FP64 x 11 (57
-    // MB) 19.8, 14.9; FP32 x 32 (83 MB) 23.8, 20.4; FP64 x 32 (165 MB) 37.2,
-    // 33.7; FP32 x 100 (258 MB) 63.0, 64.4; FP64 x 100 (516 MB) 105, 121.
     const char *nt = std::getenv("UQ_NT_STORE");
-    if (s.layout == UQ_LAYOUT_AB && !(nt && *nt)) {
-        const int64_t slab = S * 9 * (p.ny * row_pitch(p.nx) + s.pad) * storage_bytes(p.precision);
-        s.nt = 2 * slab > ((int64_t)200 << 20);
-    }
+    if (s.layout == UQ_LAYOUT_AB && !(nt && *nt))
+        s.nt = stores_bypass(S * 9 * (p.ny * row_pitch(p.nx) + s.pad) * storage_bytes(p.precision));
     return s;
 }
 
@@ -391,8 +391,12 @@ hipError_t Job::enqueue_steps(int k0, int64_t n) {
             k += m;
         }
     }
+    // (the fused shapes' nt is that of their own stores; FP64 300 x 190 x 100 187
+    // -> 175 us for a call of one step, FP32 channel 440 x 82 x 300 186 -> 173)
+    StepShape one = shape;
+    if (N) one.nt = stores_bypass(S * 9 * jd.plane * storage_bytes(p.precision));
     for (; k < n && e == hipSuccess; ++k) {
-        e = launch_step(jd, d_t, (int)(k0 + k), (int)((t + k0 + k) & 1), shape, stream);
+        e = launch_step(jd, d_t, (int)(k0 + k), (int)((t + k0 + k) & 1), one, stream);
         ++enqueued;
     }
     return e;
