@@ -54,7 +54,17 @@ typedef enum {
  * pull from one and write aligned to the other (twice the memory, higher
  * HBM rate on MI355X). AUTO: the launch-shape tuner's choice for the
  * problem class; without one, AB where a pipeline of several steps per launch
- * carries the job (and both slabs find room), else AA; UQ_LAYOUT overrides. */
+ * carries the job faster than one step per launch in AA would (and both slabs
+ * find room with a quarter of the card left free; slabs up to 256 MiB need only
+ * fit), else AA; UQ_LAYOUT overrides. That second slab doubles the job's
+ * footprint. It is given back when an allocation of the library fails (a job's
+ * buffers, a server's arena): the job then runs on in AA, with the same results,
+ * and uq_job_info shows it. A job whose steps a caller captured into a graph of
+ * its own keeps both slabs. Memory that others on the card will want (the
+ * caller's own tensors, other processes) is not seen: ask for AA to keep to one
+ * slab. Memory that a caller's allocator keeps cached counts as taken. A program
+ * that runs one to four steps per call is also better off in AA where one slab
+ * fits the 256 MB cache and two do not (up to 24 %). */
 typedef enum { UQ_LAYOUT_AUTO = 0, UQ_LAYOUT_AA = 1, UQ_LAYOUT_AB = 2 } uq_layout;
 
 /* Deterministic problem solved for every sample. */
@@ -278,7 +288,8 @@ typedef struct {
     int32_t K;          /* gPC terms (0 for MC)                        */
     int64_t steps_done; /* LBM steps taken so far                      */
     int64_t pitch;      /* row pitch of a population plane (elements)  */
-    int64_t device_bytes; /* device memory held by the job            */
+    int64_t device_bytes; /* device memory held by the job (less after an
+                             AUTO job gave back its second slab)       */
     int32_t scale_exp;  /* FP16S storage scale 2^scale_exp (else 0)    */
     int32_t fluid_nodes;
     int32_t layout;     /* uq_layout in use (AA or AB)                 */
@@ -352,7 +363,8 @@ uq_status uq_moments(uq_job *job, int32_t qoi, uq_moments_out *out);
  * QoIs, the moment outputs and a flag -- in a fixed array of
  * UQ_NOALLOC_SCRATCH_BYTES that the library keeps on every GPU it runs on
  * until the process ends, instead of buffers the job would allocate on its
- * first statistics call. The job's own device memory is untouched
+ * first statistics call (and the sums of samples cut into chunks in 112 KB
+ * behind it). The job's own device memory is untouched
  * (uq_job_info.device_bytes stays the same). The need is the sum of
  *   8 * 4 S, 8 * S, 8 and 8 * (K + 3) n_out bytes, each rounded up to 256
  * (field moments are formed from the populations, with no per-sample field
@@ -384,14 +396,17 @@ const char *uq_last_error(void);
  * 0 or 64 elements, cached or non-temporal AB stores, and for periodic
  * lattices in AB the fused kernels (2, 3 or 4 steps per launch: on tiles of
  * 64 x rows nodes kept in LDS between the steps, with a ring of one node per
- * extra step, rows 8 or 16, FP64 4 or 8; or as a sliding window, one wave
- * per step, down strips of at most 64 - 2(N - 1) columns or down whole rows
- * of up to 256 columns (K waves per step, one or two columns per lane,
- * N K <= 16, 3 to 8 steps where (N - 1) 21 rows fit in the LDS), in chunks of 64 or
- * 256 rows, FP64 32 or 64), and for channels in AB with half-way walls and
- * cylinder and Zou-He, wall or periodic ends the fused kernel over whole rows
- * (2 to 4 steps per launch where the LDS rows fit: FP32 N = 3 at 440
- * columns; the height cut into 1 to 8 balanced chunks) --
+ * extra step, rows 8 or 16, FP64 4 or 8; small jobs 4 to 12 or more steps on
+ * resident tiles; or as a sliding window, one wave per step, down strips of at
+ * most 64 - 2(N - 1) columns, or down whole rows (K waves per step, one or two
+ * columns per lane, N K <= 16, 3 to 8 steps where (N - 1) 21 rows fit in the LDS:
+ * 8 steps up to 256 columns, FP64 6 up to 128) or strips of such rows where 8
+ * steps do not fit (6 or 8 steps), in chunks of 256 or 64 rows, FP64 32 or 64,
+ * and of the height that a count of rounds gives), and for channels in AB with
+ * half-way walls and cylinder and Zou-He, wall or periodic ends the fused kernel
+ * over whole rows (2 to 4 steps per launch where the LDS rows fit: FP32 N = 3 at
+ * 440 columns; the height cut into 1 to 8 balanced chunks) or strips (7 or 8,
+ * FP64 6 or 7); last the pipeline that an untuned job of the class would take --
  * over `steps` steps each (at least 120; rounded down to whole launches of a
  * fused kernel: N steps, 2N for even N), on
  * dev's device with temporary jobs. The fastest becomes the shape of every later job of the
@@ -409,7 +424,7 @@ typedef struct {
                            its steps, so for those it exceeds the traffic)      */
     double ms_per_step; /* its average step duration                           */
     int32_t n_candidates;
-    int32_t fused;      /* steps per launch of the best if fused (2..8), else 0 */
+    int32_t fused;      /* steps per launch of the best if fused (2..16), else 0 */
     int32_t fused_rows; /* its tile height (window: chunk height)              */
     int32_t fused_window; /* as in uq_job_info                                */
 } uq_tune_result;
@@ -427,11 +442,13 @@ uq_status uq_autotune(const uq_problem *p, const uq_device *dev, int64_t steps, 
  * periodic ends in single-precision storage run in the AB layout, N steps
  * per launch over whole rows (N from the launch-shape tuner's measurement of
  * the job's class when it has one, else the largest that fits: vortex 8 or
- * 6, channel 4), one launch for all jobs that share a kernel instance;
- * lattices too wide for that run 8 steps per launch in column strips (beyond
- * 512 columns, channels 768, when their two slabs take at most two fifths of
- * the arena); the other jobs (FP64, very large ones) run in the AA layout, one launch per step for all of them. Jobs of different lattices, geometries,
- * sample counts and step parities share launches. A job with fewer steps
+ * 6, 16-bit storage 4 from 257 to 512 columns, channel 4), one launch for all
+ * jobs that share a kernel instance; lattices too wide for that run 8 steps per
+ * launch in column strips (beyond 512 columns, channels 768, where that is
+ * faster than single steps and their two slabs take at most two fifths of
+ * the arena); the other jobs (FP64, very large ones, wide ones of few rows) run
+ * in the AA layout, one launch per step for all of them. Jobs of different
+ * lattices, geometries, sample counts and step parities share launches. A job with fewer steps
  * left than a tick takes its last steps in launches of its own. PLAIN mode
  * runs one job at a time and one sample per launch per step (AA), with no
  * graph. Fused and single steps give bit for bit the same populations, so a
