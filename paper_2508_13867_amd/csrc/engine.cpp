@@ -394,7 +394,7 @@ hipError_t Job::enqueue_steps(int k0, int64_t n) {
     // (the fused shapes' nt is that of their own stores; FP64 300 x 190 x 100 187
     // -> 175 us for a call of one step, FP32 channel 440 x 82 x 300 186 -> 173)
     StepShape one = shape;
-    if (N) one.nt = stores_bypass(S * 9 * jd.plane * storage_bytes(p.precision));
+    if (N) one.nt = stores_bypass(slab_bytes());
     for (; k < n && e == hipSuccess; ++k) {
         e = launch_step(jd, d_t, (int)(k0 + k), (int)((t + k0 + k) & 1), one, stream);
         ++enqueued;

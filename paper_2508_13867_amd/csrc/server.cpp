@@ -46,7 +46,7 @@ class Arena {
                 (void)hipGetLastError();
                 base_ = nullptr;
             }
-        } while (!base_ && reclaim_slab(dev_.device));
+        } while (!base_ && reclaim_slab(dev_.device, cap_, dev_.alloc != nullptr));
         if (!base_) return fail(UQ_ENOMEM, "server arena of " + std::to_string(cap_) + " B does not fit on the device");
         free_[0] = cap_;
         return UQ_OK;

@@ -53,9 +53,22 @@ InTransit::~InTransit() {
 // comes here itself and starts with its own slab (the calling thread's own jobs
 // are taken too: an allocation is no place where a call relies on the layout).
 // The register's lock is held only to pick a job, and no callback of a caller's
-// runs under either lock: one may well destroy the job.
-bool reclaim_slab(int device) {
+// runs under either lock: one may well destroy the job. What cannot fit in any
+// case takes nobody's: more than the card has or, from hipMalloc, than is free
+// and can be given back.
+bool reclaim_slab(int device, size_t bytes, bool hooked) {
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+        (void)hipGetLastError();
+        free_b = total_b = SIZE_MAX / 4;
+    }
     std::unique_lock<std::mutex> lk(g_spare_mu);
+    size_t most = hooked ? total_b : free_b;
+    if (!hooked && g_transit == t_transit)
+        for (const Job *q : g_spare)
+            if (q->dev.device == device) most += (size_t)q->slab_bytes();
+    if (hooked || g_transit == t_transit)
+        if (bytes > most) return false;
     for (bool waited = false;; waited = true) {
         bool busy = false;
         for (size_t i = 0; i < g_spare.size(); ++i) {
@@ -100,7 +113,7 @@ void *Job::to_one_slab() {
     jd.layout = UQ_LAYOUT_AA;
     shape = StepShape();
     allocs.erase(std::find(allocs.begin(), allocs.end(), old));
-    bytes_held -= S * 9 * jd.plane * storage_bytes(p.precision);
+    bytes_held -= slab_bytes();
     return old;
 }
 
@@ -112,7 +125,7 @@ void Job::keep_slabs() {
 
 void *Job::dalloc(size_t bytes) {
     void *p = dalloc_now(bytes);
-    while (!p && reclaims && reclaim_slab(dev.device)) p = dalloc_now(bytes);
+    while (!p && reclaims && reclaim_slab(dev.device, bytes, dev.alloc != nullptr)) p = dalloc_now(bytes);
     return p;
 }
 

@@ -101,6 +101,7 @@ struct Job {
     void *dalloc(size_t bytes);
     void *dalloc_now(size_t bytes);  // without asking other jobs for memory
     void dfree(void *p);             // release one block from dalloc
+    int64_t slab_bytes() const { return S * 9 * jd.plane * storage_bytes(p.precision); }
     void *to_one_slab();             // AB to AA; the slab that is no longer needed (null: could not)
     void keep_slabs();               // out of the register
     void dfree_all();
@@ -134,8 +135,9 @@ namespace uqi {
 uq_status create_job(const uq_problem &p, const uq_device *dev, const StepShape *forced, uq_job **out,
                      bool reclaim = true);
 // One job on the device gives back the second slab that it took on its own
-// account. False if there is none to wait for.
-bool reclaim_slab(int device);
+// account, for `bytes` that hipMalloc or a caller's allocator (hooked) refused.
+// False if there is none to wait for, or none that could help.
+bool reclaim_slab(int device, size_t bytes, bool hooked);
 // While one is alive such a slab is held by a job outside the register.
 struct InTransit {
     const bool on;

@@ -239,3 +239,17 @@ def test_moving_channels_in_one_slab(xbc, steps, budget):
             got[layout] += [populations(job)]
     assert all(np.array_equal(a, b) for a, b in zip(got["ab"], got["auto"]))
     assert np.isfinite(got["ab"][1]).all() and np.abs(got["ab"][1][0, 1] - 1 / 9).max() > 1e-5
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("hooked", [True, False])
+def test_what_cannot_fit_takes_no_slab(hooked):
+    from paper_2508_13867_amd import Job, UQError
+
+    print("case too large", hooked, flush=True)
+    big = dict(VORTEX, precision="fp64", nx=1024, ny=1024, rule=dict(kind="mc", N=20000, seed=1))  # 1.5 TB
+    with Job(dict(VORTEX, precision="fp32"), torch_memory=hooked) as job:
+        assert job.info().layout == 2
+        with pytest.raises(UQError):
+            Job(big, torch_memory=hooked)
+        assert job.info().layout == 2
