@@ -110,9 +110,9 @@ double tile_steps(int prec, int nx, int ny, int64_t S, int *n_best) {
 // lattices of 2 to 1000 rows (9 of 10 of 213 shapes within 20 %). Vortices: row
 // steps, whose fill overlaps the item beside it, of 0.86 us (double 0.98, 16-bit
 // storage 1.15), 0.78 of it for items with a CU to themselves. Channels: 1.08
-// (1.25, 1.17); where all items run at once, 1.1 (1.5, 1.25) and 2 us for the
-// launch. (A chunk inside a channel also computes its halo; the whole height has
-// none.)
+// (1.25, where one wave holds both ends 1.45; 1.17); where all items run at once,
+// 1.1 (1.5, 1.25) and 2 us for the launch. (A chunk inside a channel also computes
+// its halo; the whole height has none.)
 double strips_shape(const uq_problem &p, int64_t S, StepShape *s) {
     const bool channel = p.geometry == UQ_GEOM_CHANNEL, dbl = p.precision == UQ_FP64;
     const bool half = storage_bytes(p.precision) == 2;
@@ -128,7 +128,7 @@ double strips_shape(const uq_problem &p, int64_t S, StepShape *s) {
     const double rows = std::min(s->fty, p.ny) + (r <= 1.0 && (!channel || chunks > 1) ? 3 : 2) * (s->fuse - 1);
     if (!channel) return r * rows * (dbl ? 0.98 : (half ? 1.15 : 0.86)) / s->fuse;
     return (r <= 1.0 ? rows * (dbl ? 1.5 : (half ? 1.25 : 1.1)) + 2.0
-                     : r * rows * (dbl ? 1.25 : (half ? 1.17 : 1.08))) / s->fuse;
+                     : r * rows * (dbl ? (p.nx <= 64 ? 1.45 : 1.25) : (half ? 1.17 : 1.08))) / s->fuse;
 }
 
 // A channel's pipeline: strips at the most steps per launch, or 4 steps over
