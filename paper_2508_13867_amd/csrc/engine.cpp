@@ -111,7 +111,7 @@ double tile_steps(int prec, int nx, int ny, int64_t S, int *n_best) {
 // steps, whose fill overlaps the item beside it, of 0.86 us (double 0.98, 16-bit
 // storage 1.15), 0.78 of it for items with a CU to themselves. Channels: 1.08
 // (1.25, where one wave holds both ends 1.45; 1.17); where all items run at once,
-// 1.1 (1.5, 1.25) and 2 us for the launch. (A chunk inside a channel also computes
+// 1.1 (1.5, 1.37) and 2 us for the launch. (A chunk inside a channel also computes
 // its halo; the whole height has none.)
 double strips_shape(const uq_problem &p, int64_t S, StepShape *s) {
     const bool channel = p.geometry == UQ_GEOM_CHANNEL, dbl = p.precision == UQ_FP64;
@@ -127,7 +127,7 @@ double strips_shape(const uq_problem &p, int64_t S, StepShape *s) {
     const double r = rounds_of(S * strips * chunks, per_cu, 0.78);
     const double rows = std::min(s->fty, p.ny) + (r <= 1.0 && (!channel || chunks > 1) ? 3 : 2) * (s->fuse - 1);
     if (!channel) return r * rows * (dbl ? 0.98 : (half ? 1.15 : 0.86)) / s->fuse;
-    return (r <= 1.0 ? rows * (dbl ? 1.5 : (half ? 1.25 : 1.1)) + 2.0
+    return (r <= 1.0 ? rows * (dbl ? 1.5 : (half ? 1.37 : 1.1)) + 2.0
                      : r * rows * (dbl ? (p.nx <= 64 ? 1.45 : 1.25) : (half ? 1.17 : 1.08))) / s->fuse;
 }
 
@@ -218,17 +218,20 @@ double pipeline_shape(const uq_problem &p, int64_t S, StepShape *s) {
 // Us per step of one step per launch in the AA layout: a launch's latency and
 // the longer of the memory traffic (7.5 TB/s where the slab stays in the 256 MB
 // cache, 5.5 beyond) and the lanes' issue, in ps per lane of a row's whole
-// waves (vortices also of whole 4-row tiles): channels 10 (double 13), vortices
-// 4.3 (8.3), from memory 6.5 (10.3). 9 of 10 of 466 shapes, 2 to 1470 us on
-// lattices 2 to 20000 wide x 2 to 600 samples, within 25 %.
+// waves (vortices also of whole 4-row tiles): channels 10 and 1.2 us, or 12.5 if
+// that is less (double 13), vortices 4.3 (8.3), from memory 6.5 (10.3). 9 of 10 of
+// 766 shapes, 2 to 1470 us on lattices 2 to 20000 wide x 2 to 600 samples, within
+// 25 %.
 double single_step_us(const uq_problem &p, int64_t S) {
     const bool channel = p.geometry == UQ_GEOM_CHANNEL, dbl = p.precision == UQ_FP64;
     const double b = (double)storage_bytes(p.precision), slab = 9.0 * b * (double)S * p.nx * p.ny;
     const double lanes = (double)S * (channel ? p.ny : (p.ny + 3) / 4 * 4) * (double)row_pitch(p.nx);
     const bool far = 9.0 * b * lanes > 512e6;
     const double ps = channel ? (dbl ? 13.0 : 10.0) : (dbl ? (far ? 10.3 : 8.3) : (far ? 6.5 : 4.3));
+    const double issue = lanes * ps * 1e-6;
     return (channel ? 2.9 : 2.6) + (dbl ? 0.4 : 0.0) +
-           std::max(2.0 * slab / (slab > 256e6 ? 5.5e6 : 7.5e6), lanes * ps * 1e-6);
+           std::max(2.0 * slab / (slab > 256e6 ? 5.5e6 : 7.5e6),
+                    channel && !dbl ? std::min(1.25 * issue, 1.2 + issue) : issue);
 }
 
 // The pipeline that carries a job whose shape and layout nobody chose (AB

@@ -17,6 +17,7 @@ MEASURED = [
     ("channel", "fp32", 1024, 8, 512, 45.7, 57.8), ("channel", "fp32", 4096, 3, 512, 71.1, 157),
     ("channel", "fp32", 4096, 16, 512, 437, 282), ("channel", "fp32", 100, 5, 512, 8.58, 3.56),
     ("channel", "fp64", 500, 60, 2, 4.21, 5.75), ("channel", "fp64", 500, 60, 32, 23.1, 15.1),
+    ("channel", "fp32", 264, 49, 22, 7.32, 6.18), ("channel", "fp16s", 528, 98, 3, 4.8, 5.54),
     ("channel", "fp64", 64, 512, 2, 4.29, 6.26), ("channel", "fp64", 2, 427, 143, 54.7, 67.6),
     ("channel", "fp16s", 20000, 3, 512, 363, 832),
     ("channel", "fp16s", 129, 50, 2, 3.44, 4.81), ("channel", "fp16s", 500, 60, 512, 161, 114),
