@@ -446,7 +446,8 @@ uq_status uq_autotune(const uq_problem *p, const uq_device *dev, int64_t steps, 
  * jobs that share a kernel instance; lattices too wide for that run 8 steps per
  * launch in column strips (beyond 512 columns, channels 768, where that is
  * faster than single steps and their two slabs take at most two fifths of
- * the arena); the other jobs (FP64, very large ones, wide ones of few rows) run
+ * the arena; channels between walls in x take 3 or 2 steps over whole rows
+ * instead); the other jobs (FP64, very large ones, wide ones of few rows) run
  * in the AA layout, one launch per step for all of them. Jobs of different
  * lattices, geometries, sample counts and step parities share launches. A job with fewer steps
  * left than a tick takes its last steps in launches of its own. PLAIN mode

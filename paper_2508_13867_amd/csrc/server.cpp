@@ -163,10 +163,12 @@ static ServeShape serve_shape(const uq_problem &p, int64_t S, int K, size_t aren
     // strips: their conversions make row steps dear and bytes cheap (384^2 x
     // 200 samples 85 against 103 us per step, 512^2 x 100 72 against 83; FP32
     // 98 and 86, 89 and 70)
-    const int pref[2][2] = {{p.nx <= 128 ? 6 : 8, b == 2 ? 4 : 0}, {4, 0}};
+    // (Channels between walls in x, which no batched strips take: 3 or 2.)
+    const bool walls = kind == 1 && p.xbc == UQ_XBC_WALLS;
+    const int pref[2][3] = {{p.nx <= 128 ? 6 : 8, b == 2 ? 4 : 0, 0}, {4, walls ? 3 : 0, walls ? 2 : 0}};
     StepShape tuned;
     const bool have = tuned_shape(p, S, &tuned) && tuned.fwin == 2 && tuned.fuse >= 2;
-    for (int c = -1; c < 2; ++c) {
+    for (int c = -1; c < 3; ++c) {
         const int n = c < 0 ? (have ? tuned.fuse : 0) : pref[kind][c];
         int K = 0, M = 0;
         if (n < 2 || !rows_instance(kind, p.precision, n, p.nx, &K, &M) ||
@@ -201,6 +203,7 @@ static ServeShape serve_shape(const uq_problem &p, int64_t S, int K, size_t aren
     StepShape st;
     const double us = strips_shape(p, S, &st);
     row_strips(p.precision, p.nx, 8, &sh.W, &sh.strips);
+    if (walls) return sh;
     if (p.nx > (kind == 1 ? 768 : 512) &&
         ((us >= single_step_us(p, S) && (kind == 1 || S * sh.strips > 512)) ||
          (size_t)job_footprint(p, S, K, true) > arena * 2 / 5))

@@ -173,3 +173,16 @@ def test_moving_channels_equal_single_steps(prec, xbc, nx, ny, rows, n, monkeypa
     assert np.isfinite(res[0]).all()
     assert np.abs(res[0][0, 1, :, 0] - 1 / 9).max() > 1e-5  # it does move, at the ends too
     assert np.array_equal(res[0], res[n])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nx", [300, 500, 900])
+def test_served_channels_between_walls(nx):
+    from paper_2508_13867_amd import Server
+
+    print("case served walls", nx, flush=True)
+    spec = dict(geometry="channel", precision="fp32", nx=nx, ny=20, u_peak=0.05, nu=0.02, xbc="walls",
+                dists=[("nu", 0.015, 0.025)], rule=dict(kind="gl", n=2, order=1))
+    with Server(memory_budget_gb=0.25, steps_per_tick=48, precision="fp32") as srv:
+        got = srv.wait(srv.submit(spec, 101, "ke"))
+    assert got["status"] == 0 and got["mean"] == 0.0  # at rest
